@@ -1163,6 +1163,61 @@ __device__ __forceinline__ uint32_t xshift(const XOff &o)
     return dx < 0 ? o.left : (dx > 0 ? o.right : o.at);
 }
 
+// Bit of a cell's special word (above the link bits): a shifted access of the
+// cell may cross a periodic y or z face of the domain that wraps in place.
+constexpr uint32_t kWrapBit = 0x80000000u;
+__device__ __forceinline__ uint32_t wrap_bit(const SweepArgs &a, const DevBlock &B, int y, int z)
+{
+    if (!a.wrap) return 0u;
+    const bool e = (B.wylo && y == 0) || (B.wyhi && y == B.n[1] - 1) || (B.wzlo && z == 0) || (B.wzhi && z == B.n[2] - 1);
+    return e ? kWrapBit : 0u;
+}
+// The same for a cell of tile tv: a tile away from those faces (a uniform
+// test on its box) skips the per-lane comparisons.
+__device__ __forceinline__ uint32_t wrap_bit(const SweepArgs &a, const DevBlock &B, const int4 tv, int y, int z)
+{
+    const int y0 = tv.z & 0xffff, z0 = tv.w & 0xffff;
+    const bool tile = tv.w < 0 || (B.wylo && y0 == 0) || (B.wyhi && y0 + (tv.z >> 16) == B.n[1]) || (B.wzlo && z0 == 0) ||
+                      (B.wzhi && z0 + (tv.w >> 16) == B.n[2]);
+    return tile ? wrap_bit(a, B, y, z) : 0u;
+}
+// Byte offsets of a cell's accesses shifted by any link, with all three axes
+// wrapped per lane.  They count from the first element of the domain's slot
+// (a wrapped access of a run's cell lies before the run's own first element),
+// so they are never negative, and a slot spans less than 2^31 bytes.
+struct WrapOff {
+    uint32_t x[3], y[3], z[3];  // index: shift + 1; x holds the cell's own offset
+};
+template <typename ST>
+__device__ __forceinline__ WrapOff wrap_offsets(const DevBlock &B, const XOff &o, int y, int z)
+{
+    constexpr uint32_t E = sizeof(ST);
+    const uint32_t run = (uint32_t)B.pop * E;  // the run's place in the slot
+    WrapOff w;
+    w.x[0] = run + o.left - E;
+    w.x[1] = run + o.at;
+    w.x[2] = run + o.right + E;
+    w.y[0] = (uint32_t)((y == 0 ? B.wylo : 0) - B.pitch) * E;
+    w.y[2] = (uint32_t)(B.pitch - (y == B.n[1] - 1 ? B.wyhi : 0)) * E;
+    w.z[0] = (uint32_t)((z == 0 ? B.wzlo : 0) - B.plane) * E;
+    w.z[2] = (uint32_t)(B.plane - (z == B.n[2] - 1 ? B.wzhi : 0)) * E;
+    w.y[1] = w.z[1] = 0;
+    return w;
+}
+// Address of link i's access in the wrapping form: slot sr shifted by SIGN
+// c_i, or slot ss of the cell itself where `sp` is set.
+template <int Q, typename ST, int i, int SIGN>
+__device__ __forceinline__ ST *wrap_at(const SweepArgs &a, const DevBlock &B, const WrapOff &w, int sr, int ss, bool sp)
+{
+    uint32_t reg = w.x[SIGN * cx<Q>(i) + 1];
+    if constexpr (cy<Q>(i) != 0) reg += w.y[SIGN * cy<Q>(i) + 1];
+    if constexpr (cz<Q>(i) != 0) reg += w.z[SIGN * cz<Q>(i) + 1];
+    const int lo = sr < ss ? sr : ss;
+    const uint32_t slot = (uint32_t)B.slot * (uint32_t)sizeof(ST);
+    const uint32_t off = sp ? w.x[1] + (uint32_t)(ss - lo) * slot : reg + (uint32_t)(sr - lo) * slot;
+    return at<ST>(reinterpret_cast<const char *>(a.arena) + (int64_t)lo * B.slot * (int64_t)sizeof(ST), off);
+}
+
 // Hint of an x-shifted (odd-sweep / swapped-layout) access of a population
 // with x velocity cx.  AO (aligned only): the non-temporal hint goes to the
 // accesses of populations with cx = 0, which cover whole lines per
@@ -1192,6 +1247,15 @@ __device__ __forceinline__ void gather(const SweepArgs &a, const DevBlock &B, ui
                 constexpr int i = decltype(I)::value;
                 const Alt<ST> p = alt_in<Q, ST, i>(a, B);
                 f[i] = ldv<Q, ST, nt_shifted<NT, cx<Q>(i), AO>()>(at<ST>(p.base + p.add_reg, xshift<-cx<Q>(i)>(o)), i);
+            });
+        } else if (__any(special & kWrapBit)) {
+            // some lane sits at a periodic face of the domain: offsets
+            // wrapped per lane along every axis
+            const WrapOff w = wrap_offsets<ST>(B, o, y, z);
+            sfor<Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                f[i] = ldv<Q, ST, nt_shifted<NT, cx<Q>(i), AO>()>(
+                    wrap_at<Q, ST, i, -1>(a, B, w, opp(i), i, (special >> opp(i)) & 1u), i);
             });
         } else {
             sfor<Q>([&](auto I) {
@@ -1250,6 +1314,13 @@ __device__ __forceinline__ void scatter(const SweepArgs &a, const DevBlock &B, u
                 constexpr int i = decltype(I)::value;
                 const Alt<ST> p = alt_out<Q, ST, i>(a, B);
                 stv_sr<Q, ST, nt_shifted<NT, cx<Q>(i), AO>()>(at<ST>(p.base + p.add_reg, xshift<cx<Q>(i)>(o)), f[i], i, h);
+            });
+        } else if (__any(special & kWrapBit)) {
+            const WrapOff w = wrap_offsets<ST>(B, o, y, z);
+            sfor<Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                stv_sr<Q, ST, nt_shifted<NT, cx<Q>(i), AO>()>(
+                    wrap_at<Q, ST, i, 1>(a, B, w, i, opp(i), (special >> i) & 1u), f[i], i, h);
             });
         } else {
             sfor<Q>([&](auto I) {
@@ -1374,7 +1445,7 @@ __device__ __forceinline__ void sweep_tiles(const SweepArgs &a)
         if (!kMoveSolid && solid) continue;
         const Links<Q> L = classify<Q>(mask, B, c.x, c.y, c.z, a);
         const uint32_t off = cell_off(B, c.x, c.y, c.z);
-        const uint32_t special = L.bb | L.alo | L.ahi;
+        const uint32_t special = L.bb | L.alo | L.ahi | (ODD ? wrap_bit(a, B, tv, c.y, c.z) : 0u);
         T f[Q];
         gather<Q, ST, ODD, NT, AO>(a, B, off, c.x, c.y, c.z, special, f);
         const uint32_t h = kStochastic<ST> ? state_hash<Q, T>(f, global_cell(a, B, c.x, c.y, c.z)) : 0u;
@@ -1838,7 +1909,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         if (c.valid && B.mask >= 0) mask = a.masks[B.mask + (int64_t)c.z * B.mplane + c.y * B.mpitch + c.x];
         const bool active = c.valid && !(mask & kSolidBit);
         const Links<Q> L = classify<Q>(mask, B, c.x, c.y, c.z, a);
-        const uint32_t special = L.bb | L.alo | L.ahi;
+        const uint32_t special = L.bb | L.alo | L.ahi | (ODD ? wrap_bit(a, B, tv, c.y, c.z) : 0u);
         const uint32_t off = active ? cell_off(B, c.x, c.y, c.z) : 0u;
         T f[Q];
         if (active) {
@@ -1932,7 +2003,7 @@ __global__ __launch_bounds__(kWG) void moments_kernel(const MomArgs ma)
                 const Links<Q> L = classify<Q>(mask, B, c.x, c.y, c.z, a);
                 const uint32_t off = cell_off(B, c.x, c.y, c.z);
                 typename Codec<ST>::T f[Q];
-                gather<Q, ST, SWAPPED>(a, B, off, c.x, c.y, c.z, L.bb | L.alo | L.ahi, f);
+                gather<Q, ST, SWAPPED>(a, B, off, c.x, c.y, c.z, L.bb | L.alo | L.ahi | wrap_bit(a, B, c.y, c.z), f);
                 double drho = 0, j[3] = {0, 0, 0};
                 sfor<Q>([&](auto I) {
                     constexpr int i = decltype(I)::value;
@@ -2011,7 +2082,7 @@ __global__ __launch_bounds__(kWG) void filter_kernel(const SweepArgs a, int fac,
                     if (mask & kSolidBit) continue;
                     const Links<Q> L = classify<Q>(mask, B, x, y, z, a);
                     typename Codec<ST>::T f[Q];
-                    gather<Q, ST, SWAPPED>(a, B, cell_off(B, x, y, z), x, y, z, L.bb | L.alo | L.ahi, f);
+                    gather<Q, ST, SWAPPED>(a, B, cell_off(B, x, y, z), x, y, z, L.bb | L.alo | L.ahi | wrap_bit(a, B, y, z), f);
                     double drho = 0, j[3] = {0, 0, 0};
                     sfor<Q>([&](auto I) {
                         constexpr int i = decltype(I)::value;
@@ -2110,7 +2181,7 @@ __global__ __launch_bounds__(kWG) void pdfs_kernel(const SweepArgs a, double *bu
         } else {
             const Links<Q> L = classify<Q>(mask, B, c.x, c.y, c.z, a);
             T f[Q];
-            gather<Q, ST, SWAPPED>(a, B, off, c.x, c.y, c.z, L.bb | L.alo | L.ahi, f);
+            gather<Q, ST, SWAPPED>(a, B, off, c.x, c.y, c.z, L.bb | L.alo | L.ahi | wrap_bit(a, B, c.y, c.z), f);
             for (int i = 0; i < Q; ++i) buf[i * S + k] = (double)f[i];
         }
     }

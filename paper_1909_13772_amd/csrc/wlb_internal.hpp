@@ -25,7 +25,13 @@ constexpr int kWG = 256;  // threads per workgroup of every sweep kernel
 // (xoff 0, rows back to back when the row length is a multiple of 128
 // bytes); shorter rows are packed with only their ghost cells (xoff 1):
 //   element(i, x, y, z) = pop + i * slot + (z + 1) * plane + (y + gy) * pitch + xoff + x
-// for z in [-1, n2], y in [-gy, n1 - 1 + gy].  Besides one descriptor per
+// for z in [-1, n2], y in [-gy, n1 - 1 + gy].  Where one slot of the whole
+// domain stays below 2 GiB, the runs are laid out as parts of one array over
+// the domain (the same formula with the domain's rows and planes, ghost layer
+// only around the domain): a population that crosses a face between two runs
+// is then the neighbour's own element, and nothing is copied between blocks.
+// Larger domains give every run an array with its own ghost layer, which the
+// exchange keeps consistent.  Besides one descriptor per
 // block (used by the ghost exchange), each x-run has a descriptor of its own
 // that describes the run as one block (row length W = sum of its blocks' n0,
 // the run's x ends and mask); the sweeps and every other tile-based kernel
@@ -36,7 +42,7 @@ struct DevBlock {
     int64_t slot;   // elements per population slot
     int64_t mask;   // index of interior cell (0,0,0) in the u32 mask array; -1 = block has no solid
     int32_t pitch;  // elements per row
-    int32_t plane;  // elements per z-plane = pitch * (n1 + 2)
+    int32_t plane;  // elements per z-plane of the array the block is part of
     int32_t n[3];   // interior extent
     int32_t g[3];   // global coordinates of interior cell (0,0,0)
     int32_t mpitch; // mask elements per row (interior only)
@@ -47,9 +53,14 @@ struct DevBlock {
     int32_t gy;     // 1: ghost rows on the y faces (the block exchanges along y), 0: none
     int32_t wraplo; // elements added to an access one cell below x = 0 (the run wraps), else 0
     int32_t wraphi; // elements subtracted from an access one cell above x = n0 - 1, else 0
+    // one array for the whole domain (wlb_blocks::unified): elements added to
+    // an access one row below y = 0 / one plane below z = 0, and subtracted
+    // from one a row above y = n1 - 1 / a plane above z = n2 - 1, of a run at
+    // a periodic face of the domain; else 0
+    int32_t wylo, wyhi, wzlo, wzhi;
     int32_t pad_;
 };
-static_assert(sizeof(DevBlock) == 96, "DevBlock layout");
+static_assert(sizeof(DevBlock) == 112, "DevBlock layout");
 
 // One tile of a sweep: block id and start/extent (extent <= 256 cells).
 // Packed as int4 {block, x0 | ex << 16, y0 | ey << 16, z0 | ez << 16}.  A
@@ -100,6 +111,8 @@ struct SweepArgs {
     int32_t xcd_map;       // 1: one workgroup per tile, each XCD takes a contiguous range of tiles
     int32_t nt;            // 1: the sweep's population accesses carry the non-temporal hint; 2 (odd
                            // sweep): only its aligned ones (populations with c_x = 0)
+    int32_t wrap;          // 1: shifted accesses across a periodic y / z face of the domain go straight
+                           // to its other side (DevBlock::wylo ...), no ghost layer is read or written
     int32_t vec_odd;       // 1: the odd sweep moves whole rows as 16-byte vectors per lane (vtiles)
     int32_t nvtiles;
     const int4 *vtiles;    // row tiles of the vector odd sweep: {block, 0 | n0 << 16, y0 | ey << 16, z0 | ez << 16}

@@ -1,0 +1,97 @@
+"""Block sets laid out as one array over the domain, whose direct sweeps wrap
+periodic faces in place, against the separate arrays with a ghost exchange,
+the other odd-sweep kernels and the oracle."""
+import numpy as np
+import pytest
+
+from gpu_util import gpu_run, oracle_params, oracle_run, pop_err, rel_l2, say
+from paper_1909_13772_amd import inputs, wlb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("periodic", [(1, 1, 1), (1, 0, 1)])
+def test_separate_arrays_match_one_array(periodic):
+    """Short rows padded to more than 2 GiB per slot keep one array per x-run
+    and the exchange; the undivided domain is one array.  Populations agree
+    bit for bit after an odd and an even number of steps."""
+    dom = (2, 2400, 2400)
+    say(f"case separate arrays {periodic}")
+    rho, u = inputs.random_state(dom, seed=1, umag=0.01)
+    p = wlb.make_params(tau=0.7, magic=3 / 16, force=(1e-5, 0.0, 1e-6))
+    blocks, _ = inputs.rectilinear_blocks([2], [1000, 1400], [1100, 1300])
+    got = []
+    for bl in (blocks, wlb.single_block(dom)):
+        B = wlb.Blocks(bl, dom, periodic, stencil=9, storage=wlb.F32)
+        try:
+            B.init(wlb.TRT, p, rho, u)
+            out = []
+            for n in (3, 1):
+                B.step(n)
+                out.append(B.pdfs_get())
+            B.set_kernel_timing(True)
+            B.step(2)
+            got.append((out, B.kernel_times()[1]))
+        finally:
+            B.close()
+    assert got[0][1][2:] == [1, 1] and got[1][1][2:] == [0, 0]  # exchanges of the separate arrays only
+    for a, b in zip(got[0][0], got[1][0]):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("first,second", [(0, 1), (1, 0), (0, 2), (2, 0), (1, 2)])
+@pytest.mark.parametrize("mode", ["step", "split"])
+def test_odd_sweep_kernel_changes_between_steps(first, second, mode):
+    """Odd-sweep kernels with and without the ghost layer follow each other
+    at any step, also between the two halves of a pair."""
+    dom = (32, 20, 12)
+    say(f"case kernel change {first}->{second} {mode}")
+    rho, u = inputs.random_state(dom, seed=2, umag=0.01)
+    p = wlb.make_params(tau=0.7, magic=3 / 16, force=(1e-5, 0.0, 1e-6))
+    blocks, _ = inputs.rectilinear_blocks([16, 16], [8, 12], [12])
+
+    def advance(B, n):
+        if mode == "step":
+            B.step(n)
+        else:
+            for _ in range(n):
+                B.sweep()
+                B.exchange()
+
+    ref = gpu_run(blocks, dom, (1, 1, 1), 19, wlb.F64, wlb.TRT, p, rho, u, steps=9)
+    ref[4].close()
+    for before in (1, 2, 3, 4):
+        B = wlb.Blocks(blocks, dom, (1, 1, 1), stencil=19, storage=wlb.F64)
+        try:
+            B.init(wlb.TRT, p, rho, u)
+            B.set_lds_staging(first)
+            advance(B, before)
+            B.set_lds_staging(second)
+            r, uu, _ = B.moments()
+            advance(B, 9 - before)
+            B.exchange()  # repeating the last exchange changes nothing
+            assert np.array_equal(B.pdfs_get(), ref[0]), before
+        finally:
+            B.close()
+
+
+@pytest.mark.parametrize("ny,nz", [([1], [2]), ([2], [1]), ([1, 2], [2]), ([1, 4], [2, 1, 3]), ([10, 6], [7, 9])])
+@pytest.mark.parametrize("nx", [5, 70, 130])
+@pytest.mark.parametrize("q,coll", [(19, 1), (27, 2)])
+def test_wrapping_in_place_at_small_extents(nx, ny, nz, q, coll):
+    """Periodic extents of one to three cells (a cell may sit at both faces of
+    an axis), runs away from the domain's origin, short packed rows and rows
+    of several wavefronts: FP64 parity with the oracle, which keeps no ghost
+    layer and streams by index."""
+    blocks, dom = inputs.rectilinear_blocks([nx], ny, nz)
+    say(f"case wrap {dom} {ny} {nz} q{q}")
+    rho, u = inputs.random_state(dom, seed=3, umag=0.02)
+    F = (1e-5, -1e-5, 2e-6)
+    p = wlb.make_params(tau=0.7, magic=3 / 16, omega_bulk=1.1, force=F)
+    for periodic in ((1, 1, 1), (0, 1, 1), (1, 0, 1)):
+        for steps in (4, 5):
+            d, r, uu, _, B = gpu_run(blocks, dom, periodic, q, wlb.F64, coll, p, rho, u, steps=steps)
+            B.close()
+            op = oracle_params(q, coll, 0.7, 3 / 16, periodic, F, omega_bulk=1.1)
+            do, ro, uo, _ = oracle_run(op, dom, rho, u, None, steps)
+            assert pop_err(d, do, q) <= 1e-12 and rel_l2(uu.reshape(3, -1), uo) <= 1e-12, (periodic, steps)
