@@ -17,6 +17,7 @@
 
 #include "../../include/wlb.h"
 #include "lattice.hpp"
+#include "transfer.hpp"
 #include "wlb_internal.hpp"
 
 using namespace wlb;
@@ -132,6 +133,7 @@ struct wlb_blocks {
     bool tiles_split = false;
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    PinnedRing ring;  // pinned buffers of the host transfers
     bool use_graph = true;
     hipGraphExec_t gexec = nullptr;
     hipGraph_t graph = nullptr;
@@ -736,16 +738,17 @@ int do_init_state(wlb_blocks *h, const double *rho, const double *u)
     const int64_t N = plane * h->dom[2];
     const int kz = planes_per_chunk(h, 4 * sizeof(double));
     double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
+    HostCopy up(h->ring, false, h->stream, 4 * sizeof(double) * N);
     for (int z0 = 0; z0 < h->dom[2]; z0 += kz) {
         const int z1 = std::min(h->dom[2], z0 + kz);
         const int64_t S = (int64_t)(z1 - z0) * plane;
-        HIPCHK(hipMemcpyAsync(stage, rho + z0 * plane, S * sizeof(double), hipMemcpyHostToDevice, h->stream));
+        HIPCHK(up.add(const_cast<double *>(rho) + z0 * plane, stage, S * sizeof(double)));
         for (int a = 0; a < 3; ++a)
-            HIPCHK(hipMemcpyAsync(stage + (1 + a) * S, u + a * N + z0 * plane, S * sizeof(double),
-                                  hipMemcpyHostToDevice, h->stream));
+            HIPCHK(up.add(const_cast<double *>(u) + a * N + z0 * plane, stage + (1 + a) * S, S * sizeof(double)));
+        HIPCHK(up.flush());
         HIPCHK(init_dispatch(h, stage, z0, z1, aux_grid(h)));
-        HIPCHK(hipStreamSynchronize(h->stream));
     }
+    HIPCHK(hipStreamSynchronize(h->stream));
     h->steps = 0;
     h->parity = 0;
     h->pending = 0;
@@ -1685,6 +1688,7 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
         const int64_t N = plane * h->dom[2];
         const int kz = planes_per_chunk(h, 4 * sizeof(double));
         double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
+        HostCopy down(h->ring, true, h->stream, ((rho ? 1 : 0) + (u ? 3 : 0)) * sizeof(double) * N);
         for (int z0 = 0; z0 < h->dom[2]; z0 += kz) {
             const int z1 = std::min(h->dom[2], z0 + kz);
             const int64_t S = (int64_t)(z1 - z0) * plane;
@@ -1696,13 +1700,13 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
             m.out = stage;
             m.partials = nullptr;
             HIPCHK(moments_dispatch(h, m, aux_grid(h)));
-            if (rho) HIPCHK(hipMemcpyAsync(rho + z0 * plane, stage, S * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+            if (rho) HIPCHK(down.add(rho + z0 * plane, stage, S * sizeof(double)));
             if (u)
                 for (int a = 0; a < 3; ++a)
-                    HIPCHK(hipMemcpyAsync(u + a * N + z0 * plane, stage + (1 + a) * S, S * sizeof(double),
-                                          hipMemcpyDeviceToHost, h->stream));
-            HIPCHK(hipStreamSynchronize(h->stream));
+                    HIPCHK(down.add(u + a * N + z0 * plane, stage + (1 + a) * S, S * sizeof(double)));
         }
+        HIPCHK(down.flush());
+        HIPCHK(hipStreamSynchronize(h->stream));
     }
     return WLB_OK;
 }
@@ -1762,22 +1766,19 @@ static int pdfs_io(wlb_blocks_t h, double *d, bool to_dev)
     const int64_t N = plane * h->dom[2];
     const int kz = planes_per_chunk(h, h->q * sizeof(double));
     double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
+    HostCopy link(h->ring, !to_dev, h->stream, h->q * sizeof(double) * N);
     for (int z0 = 0; z0 < h->dom[2]; z0 += kz) {
         const int z1 = std::min(h->dom[2], z0 + kz);
         const int64_t S = (int64_t)(z1 - z0) * plane;
+        if (!to_dev) HIPCHK(pdfs_dispatch(h, stage, z0, z1, false, h->parity == 1, aux_grid(h)));
+        for (int i = 0; i < h->q; ++i) HIPCHK(link.add(d + i * N + z0 * plane, stage + i * S, S * sizeof(double)));
         if (to_dev) {
-            for (int i = 0; i < h->q; ++i)
-                HIPCHK(hipMemcpyAsync(stage + i * S, d + i * N + z0 * plane, S * sizeof(double),
-                                      hipMemcpyHostToDevice, h->stream));
+            HIPCHK(link.flush());
             HIPCHK(pdfs_dispatch(h, stage, z0, z1, true, false, aux_grid(h)));
-        } else {
-            HIPCHK(pdfs_dispatch(h, stage, z0, z1, false, h->parity == 1, aux_grid(h)));
-            for (int i = 0; i < h->q; ++i)
-                HIPCHK(hipMemcpyAsync(d + i * N + z0 * plane, stage + i * S, S * sizeof(double),
-                                      hipMemcpyDeviceToHost, h->stream));
         }
-        HIPCHK(hipStreamSynchronize(h->stream));
     }
+    HIPCHK(link.flush());
+    HIPCHK(hipStreamSynchronize(h->stream));
     if (to_dev) {
         h->parity = 0;
         h->pending = 0;

@@ -1993,6 +1993,10 @@ __global__ __launch_bounds__(kWG) void moments_kernel(const MomArgs ma)
         const int4 tv = a.tiles[t];
         const CellPos c = tile_cell(tv, threadIdx.x);
         const DevBlock B = a.blocks[tv.x];
+        if (!ma.partials) {  // fields of a z slab only: the other tiles have nothing to do
+            const int zt = B.g[2] + (tv.w & 0xffff);
+            if (zt >= ma.z1 || zt + (tv.w >> 16) <= ma.z0) continue;
+        }
         double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // drho, px, py, pz, ke, umax, nfluid, -
         if (c.valid) {
             uint32_t mask = 0;

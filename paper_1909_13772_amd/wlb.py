@@ -383,15 +383,15 @@ class Blocks:
         nx, ny, nz = self.domain
         tot = np.zeros(8)
         if fields:
-            rho = np.zeros(self.ncells)
-            u = np.zeros(3 * self.ncells)
+            rho = np.empty(self.ncells)  # every cell is written
+            u = np.empty(3 * self.ncells)
             wlb_moments_get(self.h, rho, u, tot)
             return rho.reshape(nz, ny, nx), u.reshape(3, nz, ny, nx), tot
         wlb_moments_get(self.h, None, None, tot)
         return None, None, tot
 
     def pdfs_get(self):
-        d = np.zeros(self.stencil * self.ncells)
+        d = np.empty(self.stencil * self.ncells)  # every entry is written
         wlb_pdfs_get(self.h, d)
         return d.reshape(self.stencil, self.ncells)
 
