@@ -90,14 +90,6 @@ __device__ __forceinline__ HalfErfc half_erfc_parts(float z)
     return HalfErfc{t, __builtin_amdgcn_exp2f(fmaf(-v, v, p))};
 }
 
-// Standard normal CDF: Phi(z) = 1 - Phi(-z) for z >= 0.
-__device__ __forceinline__ float norm_cdf(float z)
-{
-    const HalfErfc h = half_erfc_parts(z);
-    const float half_erfc = h.t * h.e;
-    return z >= 0.f ? 1.0f - half_erfc : half_erfc;
-}
-
 // GELU with the exact Gaussian CDF, z Phi(z) = max(z, 0) - |z| Phi(-|z|):
 // one multiply, one max and one fused multiply-add after the CDF's parts.
 __device__ __forceinline__ float gelu_erf(float z)

@@ -3,13 +3,13 @@
 //
 // Loss over a minibatch of n samples: L = (1/n) sum_s ((softplus(o_s) - t_s)
 // * inv_scale)^2, o = network output for the sample's raw features (see
-// mlp.hpp for the network).  The forward/backward pass runs one sample per
-// thread in FP32 with the GEMM operands (weights, x, h1, h2) rounded to bf16
-// exactly where the matrix-core forward rounds them; the rounding has the
-// straight-through gradient.  Parameter gradients are summed per workgroup
-// through LDS in a fixed order, then over workgroups in a fixed order
-// (deterministic).  Adam keeps FP32 master weights; mean / inv_std are not
+// mlp.hpp for the network).  The GEMM operands (weights, x, h1, h2) are rounded
+// to bf16 exactly where the sweep's forward rounds them; the rounding has the
+// straight-through gradient, and the gradients themselves keep FP32 precision.
+// Parameter gradients are summed per workgroup in a fixed order, then over
+// workgroups in a fixed order (deterministic).  Adam keeps FP32 master weights; mean / inv_std are not
 // trained.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -22,131 +22,259 @@ constexpr int kIn = 7, kH = 32;
 constexpr int kOffMean = 0, kOffIstd = 7, kOffW1 = 14, kOffB1 = kOffW1 + kH * kIn, kOffW2 = kOffB1 + kH,
               kOffB2 = kOffW2 + kH * kH, kOffW3 = kOffB2 + kH, kOffB3 = kOffW3 + kH, kNParam = kOffB3 + 1;
 static_assert(kNParam == 1359, "parameter count");
-constexpr int kChunk = 64;  // samples staged in LDS at a time
-
-__device__ __forceinline__ float gelu_grad(float z)
+// GELU and its slope at z, from one evaluation of the CDF's parts.
+__device__ __forceinline__ void gelu_and_slope(float z, float &g, float &slope)
 {
-    return norm_cdf(z) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+    const HalfErfc h = half_erfc_parts(z);
+    g = fmaf(-(fabsf(z) * h.t), h.e, fmaxf(z, 0.f));
+    const float tail = h.t * h.e;
+    slope = (z >= 0.f ? 1.0f - tail : tail) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 __device__ __forceinline__ float sigmoid_f(float o) { return 1.0f / (1.0f + expf(-o)); }
 
-// One sample per thread; per-workgroup gradient partials [gridDim.x][kNParam + 1]
-// (last entry: sum of squared residuals).
-__global__ __launch_bounds__(kWG) void mlp_grad_kernel(const float *__restrict__ P, const float *__restrict__ raw,
-                                                        const float *__restrict__ target, int64_t n, float inv_scale,
-                                                        float *__restrict__ partial)
+// x as the sum of three bf16 values (8 + 8 + 8 significand bits: nothing of
+// an FP32 value is lost; the differences are exact).  A value that bf16
+// rounds to infinity keeps it in the first part alone.
+struct Split3 {
+    __bf16 p[3];
+};
+__device__ __forceinline__ Split3 split3(float x)
 {
-    __shared__ float sw[kNParam];  // bf16-rounded weights, FP32 biases
-    __shared__ float s_xb[kChunk][8];
-    __shared__ float s_h1b[kChunk][kH];
-    __shared__ float s_gz1[kChunk][kH];
-    __shared__ float s_h2b[kChunk][kH];
-    __shared__ float s_gz2[kChunk][kH];
-    __shared__ float s_go[kChunk];
-    __shared__ float s_loss[kWG];
-    for (int k = threadIdx.x; k < kNParam; k += kWG) {
-        const bool is_w = (k >= kOffW1 && k < kOffB1) || (k >= kOffW2 && k < kOffB2) || (k >= kOffW3 && k < kOffB3);
-        sw[k] = is_w ? bf16_round(P[k]) : P[k];
-    }
+    Split3 r;
+    r.p[0] = (__bf16)x;
+    float d = x - (float)r.p[0];
+    d = fabsf(x) < 3e38f ? d : 0.f;
+    r.p[1] = (__bf16)d;
+    r.p[2] = (__bf16)(d - (float)r.p[1]);
+    return r;
+}
+
+constexpr int kGradWG = 512;        // eight wavefronts, each one tile of 32 samples at a time
+constexpr int kGradWaves = kGradWG / 64;
+constexpr int kTileS = 32;          // samples of a wavefront's tile
+constexpr int kMaxGradWG = 512;     // partial rows; larger minibatches loop
+constexpr int kRow = kTileS + 8;    // bf16 per LDS row: 16-byte aligned 8-sample reads, rows spread over the banks
+// LDS rows of a wavefront's tile, each one quantity of its 32 samples
+constexpr int kRowG = 0, kRowH1 = 96, kRowH2 = 128, kRowX = 160, kRowGo = 168, kRows = 171;
+
+typedef __bf16 bf16row_t[kRow];
+
+// Eight consecutive samples of a row as a matrix operand.
+__device__ __forceinline__ bf16x8_t row8(const bf16row_t &r, int s) { return *reinterpret_cast<const bf16x8_t *>(&r[s]); }
+
+// Forward and backward pass of the network over a minibatch on the matrix
+// cores; per-workgroup gradient partials [gridDim.x][kNParam + 1] (last
+// entry: sum of squared residuals).
+//
+// A wavefront takes 32 samples.  Forward (mlp.hpp's layout): lane l holds the
+// sample l % 32 and, in its result registers j, the hidden units mlp_unit(j,
+// l / 32); one layer's registers are the next product's operand.  The same
+// holds for the backward product with W2^T, whose other operand is FP32: it
+// enters as three bf16 parts (split3), three products instead of one, so
+// nothing of its 24 bits is lost.  The weight gradients contract over the
+// samples: both operands are turned through LDS (rows of one quantity, 32
+// samples) and summed over all of a wavefront's tiles in the accumulators of
+// dW2 = gz2^T h1, dW1 and db1 = gz1^T [x | 1], db2 = gz2^T [x | 1], dw3 = h2^T go.
+//
+// What bounds it: the activations (GELU and its slope, 64 per sample) on the
+// vector ALUs, some 1,700 instructions per tile against 23 matrix products of
+// 32 cycles.  16,384 samples: 64 workgroups of eight wavefronts, one tile each.
+// One sample per thread on the vector ALUs with the sums read back from LDS
+// took 86 us for that minibatch.
+__global__ __launch_bounds__(kGradWG) void mlp_grad_kernel(const float *__restrict__ P, const float *__restrict__ raw,
+                                                           const float *__restrict__ target, int64_t n,
+                                                           float inv_scale, float *__restrict__ partial)
+{
+    constexpr size_t kTileBytes = sizeof(__bf16) * kGradWaves * kRows * kRow;
+    constexpr size_t kRedBytes = sizeof(float) * kGradWaves * (kNParam + 1);
+    __shared__ __align__(16) unsigned char smem[kTileBytes > kRedBytes ? kTileBytes : kRedBytes];
+    __shared__ float sw[kNParam];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int m = lane & 31, h = lane >> 5;
+    for (int k = threadIdx.x; k < kNParam; k += kGradWG) sw[k] = P[k];
     __syncthreads();
-    const int64_t s = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    const bool act = s < n;
-    // ---- forward
-    float xb[8], z1[kH], h1b[kH], z2[kH], h2b[kH];
-    for (int k = 0; k < kIn; ++k) {
-        const float r = act ? raw[s * kIn + k] : 0.f;
-        xb[k] = bf16_round((r - sw[kOffMean + k]) * sw[kOffIstd + k]);
-    }
-    xb[7] = 0.f;
-    for (int j = 0; j < kH; ++j) {
-        float a = 0.f;
-        for (int k = 0; k < kIn; ++k) a += sw[kOffW1 + j * kIn + k] * xb[k];
-        z1[j] = a + sw[kOffB1 + j];
-        h1b[j] = bf16_round(gelu_erf(z1[j]));
-    }
-    for (int j = 0; j < kH; ++j) {
-        float a = 0.f;
-        for (int k = 0; k < kH; ++k) a += sw[kOffW2 + j * kH + k] * h1b[k];
-        z2[j] = a + sw[kOffB2 + j];
-        h2b[j] = bf16_round(gelu_erf(z2[j]));
-    }
-    float o = 0.f;
-    for (int k = 0; k < kH; ++k) o += sw[kOffW3 + k] * h2b[k];
-    o += sw[kOffB3];
-    // ---- backward
-    const float res = act ? (softplus_f(o) - target[s]) * inv_scale : 0.f;
-    const float go = act ? 2.f * res * inv_scale * sigmoid_f(o) / (float)n : 0.f;
-    float gz2[kH], gz1[kH];
-    for (int j = 0; j < kH; ++j) gz2[j] = go * sw[kOffW3 + j] * gelu_grad(z2[j]);
-    for (int k = 0; k < kH; ++k) {
-        float a = 0.f;
-        for (int j = 0; j < kH; ++j) a += gz2[j] * sw[kOffW2 + j * kH + k];
-        gz1[k] = a * gelu_grad(z1[k]);
-    }
-    s_loss[threadIdx.x] = res * res;
-    // ---- parameter sums over the workgroup's samples, kChunk at a time
-    float acc[(kNParam + kWG - 1) / kWG];
-    for (int r = 0; r < (kNParam + kWG - 1) / kWG; ++r) acc[r] = 0.f;
-    for (int c0 = 0; c0 < kWG; c0 += kChunk) {
-        __syncthreads();
-        const int ls = (int)threadIdx.x - c0;
-        if (ls >= 0 && ls < kChunk) {
-            for (int k = 0; k < 8; ++k) s_xb[ls][k] = xb[k];
-            for (int j = 0; j < kH; ++j) {
-                s_h1b[ls][j] = h1b[j];
-                s_gz1[ls][j] = gz1[j];
-                s_h2b[ls][j] = h2b[j];
-                s_gz2[ls][j] = gz2[j];
-            }
-            s_go[ls] = go;
-        }
-        __syncthreads();
-        for (int r = 0; r < (kNParam + kWG - 1) / kWG; ++r) {
-            const int p = (int)threadIdx.x + r * kWG;
-            if (p < kOffW1 || p >= kNParam) continue;
-            float a = 0.f;
-            if (p < kOffB1) {
-                const int j = (p - kOffW1) / kIn, k = (p - kOffW1) % kIn;
-                for (int q = 0; q < kChunk; ++q) a += s_gz1[q][j] * s_xb[q][k];
-            } else if (p < kOffW2) {
-                const int j = p - kOffB1;
-                for (int q = 0; q < kChunk; ++q) a += s_gz1[q][j];
-            } else if (p < kOffB2) {
-                const int j = (p - kOffW2) / kH, k = (p - kOffW2) % kH;
-                for (int q = 0; q < kChunk; ++q) a += s_gz2[q][j] * s_h1b[q][k];
-            } else if (p < kOffW3) {
-                const int j = p - kOffB2;
-                for (int q = 0; q < kChunk; ++q) a += s_gz2[q][j];
-            } else if (p < kOffB3) {
-                const int k = p - kOffW3;
-                for (int q = 0; q < kChunk; ++q) a += s_go[q] * s_h2b[q][k];
-            } else {
-                for (int q = 0; q < kChunk; ++q) a += s_go[q];
-            }
-            acc[r] += a;
+    // operands: W1 row m (both k halves), W2 row m and W2 column m in the
+    // order in which the result registers hold the hidden units
+    bf16x8_t w1, w2[2], w2t[2];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        w1[t] = t < kIn ? (__bf16)sw[kOffW1 + m * kIn + t] : (__bf16)0.f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int unit = mlp_unit(8 * q + t, h);
+            w2[q][t] = (__bf16)sw[kOffW2 + m * kH + unit];
+            w2t[q][t] = (__bf16)sw[kOffW2 + unit * kH + m];
         }
     }
-    float *out = partial + (int64_t)blockIdx.x * (kNParam + 1);
-    for (int r = 0; r < (kNParam + kWG - 1) / kWG; ++r) {
-        const int p = (int)threadIdx.x + r * kWG;
-        if (p < kNParam) out[p] = p < kOffW1 ? 0.f : acc[r];
+    bf16row_t *T = reinterpret_cast<bf16row_t *>(smem) + wv * kRows;
+    f32x16_t dw2 = {}, dw1 = {}, db2 = {}, dw3 = {};
+    float loss = 0.f, db3 = 0.f;
+    const bf16x8_t zero = {};
+    const int64_t ntile = (n + kTileS - 1) / kTileS;
+    // every wavefront of the workgroup makes the same number of rounds
+    for (int64_t t0 = (int64_t)blockIdx.x * kGradWaves; t0 < ntile; t0 += (int64_t)gridDim.x * kGradWaves) {
+        const int64_t s = (t0 + wv) * kTileS + m;
+        const bool act = s < n;
+        // an opaque zero keeps the reads of biases and output weights inside
+        // the loop: hoisted, they would hold ~60 registers
+        int zo = 0;
+        asm volatile("" : "+v"(zo));
+        const float *sv = sw + 4 * h + zo;  // unit mlp_unit(j, h) is 8 (j / 4) + j % 4 further on
+        // ---- forward
+        bf16x8_t xb;
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {
+            const float r = act ? raw[s * kIn + k] : 0.f;
+            xb[k] = (__bf16)((r - sw[kOffMean + k + zo]) * sw[kOffIstd + k + zo]);
+        }
+        xb[7] = (__bf16)0.f;
+        f32x16_t z;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) z[j] = sv[kOffB1 + mlp_unit(j, 0)];
+        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, h == 0 ? xb : zero, z, 0, 0, 0);
+        float s1[16];  // slopes of layer 1
+        bf16x8_t hb[2];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            float g;
+            gelu_and_slope(z[j], g, s1[j]);
+            hb[j / 8][j % 8] = (__bf16)g;
+            T[kRowH1 + mlp_unit(j, h)][m] = (__bf16)g;
+            // a few activations at a time: all sixteen in flight spill
+            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) z[j] = sv[kOffB2 + mlp_unit(j, 0)];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2[q], hb[q], z, 0, 0, 0);
+        float gz[16];  // w3 times the slope of layer 2
+        float o = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const float w3 = bf16_round(sv[kOffW3 + mlp_unit(j, 0)]);
+            float g, sl;
+            gelu_and_slope(z[j], g, sl);
+            const __bf16 b = (__bf16)g;
+            T[kRowH2 + mlp_unit(j, h)][m] = b;
+            o = fmaf(w3, (float)b, o);
+            gz[j] = w3 * sl;
+            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        o += __shfl_xor(o, 32, 64);  // the other half of the units
+        o += sw[kOffB3];
+        // ---- backward
+        const float res = act ? (softplus_f(o) - target[s]) * inv_scale : 0.f;
+        const float go = act ? 2.f * res * inv_scale * sigmoid_f(o) / (float)n : 0.f;
+        if (h == 0) {
+            loss += res * res;
+            db3 += go;
+            const Split3 g3 = split3(go);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) T[kRowGo + p][m] = g3.p[p];
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) T[kRowX + k][m] = xb[k];
+            T[kRowX + kIn][m] = (__bf16)1.f;
+        }
+        bf16x8_t gb[3][2];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const Split3 g3 = split3(go * gz[j]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                gb[p][j / 8][j % 8] = g3.p[p];
+                T[kRowG + 32 * p + mlp_unit(j, h)][m] = g3.p[p];
+            }
+        }
+        f32x16_t ga = {};
+#pragma unroll
+        for (int p = 2; p >= 0; --p)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) ga = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2t[q], gb[p][q], ga, 0, 0, 0);
+        __syncthreads();
+        // ---- sums over the tile's samples, 16 at a time
+        bf16x8_t xc[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int s8 = 16 * c + 8 * h;
+            const bf16x8_t h1 = row8(T[kRowH1 + m], s8);
+            xc[c] = m < 8 ? row8(T[kRowX + (m & 7)], s8) : zero;
+            const bf16x8_t gc = m < 3 ? row8(T[kRowGo + (m < 3 ? m : 0)], s8) : zero;
+            dw3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row8(T[kRowH2 + m], s8), gc, dw3, 0, 0, 0);
+#pragma unroll
+            for (int p = 2; p >= 0; --p) {
+                const bf16x8_t g = row8(T[kRowG + 32 * p + m], s8);
+                dw2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, h1, dw2, 0, 0, 0);
+                db2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, xc[c], db2, 0, 0, 0);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const Split3 g3 = split3(ga[j] * s1[j]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) T[kRowG + 32 * p + mlp_unit(j, h)][m] = g3.p[p];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int p = 2; p >= 0; --p)
+                dw1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row8(T[kRowG + 32 * p + m], 16 * c + 8 * h), xc[c], dw1, 0, 0,
+                                                              0);
+        __syncthreads();
+    }
+    // ---- the eight wavefronts' sums, in a fixed order
+    float *red = reinterpret_cast<float *>(smem) + wv * (kNParam + 1);
+    for (int k = lane; k < kOffW1; k += 64) red[k] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {  // lane: column m of each product, rows = units
+        const int u = mlp_unit(j, h);
+        red[kOffW2 + u * kH + m] = dw2[j];
+        if (m < kIn) red[kOffW1 + u * kIn + m] = dw1[j];
+        if (m == kIn) {
+            red[kOffB1 + u] = dw1[j];
+            red[kOffB2 + u] = db2[j];
+        }
+        // the three parts of go sit in columns 0, 1, 2
+        const float a = __shfl_down(dw3[j], 1, 64), b = __shfl_down(dw3[j], 2, 64);
+        if (m == 0) red[kOffW3 + u] = (b + a) + dw3[j];
+    }
+    for (int d = 16; d > 0; d >>= 1) {
+        loss += __shfl_xor(loss, d, 64);
+        db3 += __shfl_xor(db3, d, 64);
+    }
+    if (lane == 0) {
+        red[kOffB3] = db3;
+        red[kNParam] = loss;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float l = 0.f;
-        for (int k = 0; k < kWG; ++k) l += s_loss[k];
-        out[kNParam] = l;
+    const float *all = reinterpret_cast<const float *>(smem);
+    for (int p = threadIdx.x; p <= kNParam; p += kGradWG) {
+        float a = 0.f;
+        for (int w = 0; w < kGradWaves; ++w) a += all[w * (kNParam + 1) + p];
+        partial[(int64_t)blockIdx.x * (kNParam + 1) + p] = a;
     }
 }
 
-// grad[p] = sum over workgroups (fixed order); loss = sum of squares / n.
+// grad[p] = sum over workgroups (fixed order: eight interleaved sums per
+// parameter, then those in turn); loss = sum of squares / n.  32 parameters x
+// 8 row groups per workgroup; one thread per parameter over all rows took 16
+// us for 64 rows.
+constexpr int kRedCols = 32, kRedRows = kWG / kRedCols;
 __global__ __launch_bounds__(kWG) void mlp_grad_reduce_kernel(const float *__restrict__ partial, int nwg, int64_t n,
                                                                float *__restrict__ grad, float *__restrict__ loss)
 {
-    const int p = blockIdx.x * kWG + threadIdx.x;
-    if (p > kNParam) return;
+    __shared__ float s[kRedRows][kRedCols];
+    const int c = threadIdx.x % kRedCols, g = threadIdx.x / kRedCols;
+    const int p = blockIdx.x * kRedCols + c;
     float a = 0.f;
-    for (int w = 0; w < nwg; ++w) a += partial[(int64_t)w * (kNParam + 1) + p];
+    if (p <= kNParam)
+        for (int w = g; w < nwg; w += kRedRows) a += partial[(int64_t)w * (kNParam + 1) + p];
+    s[g][c] = a;
+    __syncthreads();
+    if (g != 0 || p > kNParam) return;
+    a = 0.f;
+    for (int k = 0; k < kRedRows; ++k) a += s[k][c];
     if (p < kNParam)
         grad[p] = a;
     else
@@ -211,12 +339,13 @@ size_t mlp_grad_workspace_bytes(int64_t n)
 hipError_t launch_mlp_grad(const float *P, const float *raw, const float *target, int64_t n, float inv_scale,
                            float *grad, float *loss, float *work, hipStream_t st)
 {
-    const int64_t nwg = (n + kWG - 1) / kWG;
-    hipLaunchKernelGGL(mlp_grad_kernel, dim3((int)nwg), dim3(kWG), 0, st, P, raw, target, n, inv_scale, work);
+    // one workgroup per 256 samples (a row of the workspace each), up to two per CU
+    const int64_t nwg = std::min<int64_t>((n + kGradWaves * kTileS - 1) / (kGradWaves * kTileS), kMaxGradWG);
+    hipLaunchKernelGGL(mlp_grad_kernel, dim3((int)nwg), dim3(kGradWG), 0, st, P, raw, target, n, inv_scale, work);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mlp_grad_reduce_kernel, dim3((kNParam + 1 + kWG - 1) / kWG), dim3(kWG), 0, st, work, (int)nwg, n,
-                       grad, loss);
+    hipLaunchKernelGGL(mlp_grad_reduce_kernel, dim3((kNParam + 1 + kRedCols - 1) / kRedCols), dim3(kWG), 0, st, work,
+                       (int)nwg, n, grad, loss);
     return hipGetLastError();
 }
 
