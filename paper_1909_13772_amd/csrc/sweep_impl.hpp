@@ -2062,55 +2062,75 @@ __global__ __launch_bounds__(kWG) void moments_kernel(const MomArgs ma)
 
 // ---------------------------------------------------------------------------
 // Box filter for LES training data: averages over factor^3 fine cells of
-// rho, u (Guo velocity) and the products u_a u_b, one thread per coarse cell,
-// fixed summation order.  Single-block handles; out[10][Nc] =
-// (rho, ux, uy, uz, uxux, uyuy, uzuz, uxuy, uxuz, uyuz).
+// rho, u (Guo velocity) and the products u_a u_b, in a fixed summation order.
+// Single-block handles; out[10][Nc] = (rho, ux, uy, uz, uxux, uyuy, uzuz,
+// uxuy, uxuz, uyuz).  A workgroup takes kWG / factor neighbouring coarse cells,
+// one thread per fine x position of theirs: a wavefront reads whole lines of
+// every population, each thread sums its (y, z) column of factor^2 cells, and
+// the factor sums along x meet in LDS.  Bound by the one read of the
+// populations (256^3 FP32: 1.28 GB); with one thread per coarse cell, whose
+// lanes read elements `factor` apart, that case took 712 us.
 // ---------------------------------------------------------------------------
 template <int Q, typename ST, bool SWAPPED>
 __global__ __launch_bounds__(kWG) void filter_kernel(const SweepArgs a, int fac, double *out)
 {
+    __shared__ double sum[10][kWG];
     const DevBlock B = a.blocks[0];
     const int ncx = B.n[0] / fac, ncy = B.n[1] / fac, ncz = B.n[2] / fac;
     const int64_t Nc = (int64_t)ncx * ncy * ncz;
     const double inv = 1.0 / ((double)fac * fac * fac);
-    for (int64_t c = (int64_t)blockIdx.x * kWG + threadIdx.x; c < Nc; c += (int64_t)gridDim.x * kWG) {
-        const int X = (int)(c % ncx), Y = (int)((c / ncx) % ncy), Z = (int)(c / ((int64_t)ncx * ncy));
+    const int cells = fac < kWG ? kWG / fac : 1;  // coarse cells of a workgroup
+    const int lanes = fac < kWG ? fac : kWG;      // threads of a coarse cell
+    for (int64_t c0 = (int64_t)blockIdx.x * cells; c0 < Nc; c0 += (int64_t)gridDim.x * cells) {
+        const int64_t c = c0 + threadIdx.x / lanes;
         double acc[10];
         for (int k = 0; k < 10; ++k) acc[k] = 0.0;
-        for (int dz = 0; dz < fac; ++dz)
-            for (int dy = 0; dy < fac; ++dy)
-                for (int dx = 0; dx < fac; ++dx) {
-                    const int x = X * fac + dx, y = Y * fac + dy, z = Z * fac + dz;
-                    uint32_t mask = 0;
-                    if (B.mask >= 0) mask = a.masks[B.mask + (int64_t)z * B.mplane + y * B.mpitch + x];
-                    if (mask & kSolidBit) continue;
-                    const Links<Q> L = classify<Q>(mask, B, x, y, z, a);
-                    typename Codec<ST>::T f[Q];
-                    gather<Q, ST, SWAPPED>(a, B, cell_off(B, x, y, z), x, y, z, L.bb | L.alo | L.ahi | wrap_bit(a, B, y, z), f);
-                    double drho = 0, j[3] = {0, 0, 0};
-                    sfor<Q>([&](auto I) {
-                        constexpr int i = decltype(I)::value;
-                        const double v = (double)f[i];
-                        drho += v;
-                        if constexpr (cx<Q>(i) != 0) j[0] += cx<Q>(i) * v;
-                        if constexpr (cy<Q>(i) != 0) j[1] += cy<Q>(i) * v;
-                        if constexpr (cz<Q>(i) != 0) j[2] += cz<Q>(i) * v;
-                    });
-                    const double rho = 1.0 + drho;
-                    double u[3];
-                    for (int k = 0; k < 3; ++k) u[k] = (j[k] + 0.5 * a.force[k]) / rho;
-                    acc[0] += rho;
-                    acc[1] += u[0];
-                    acc[2] += u[1];
-                    acc[3] += u[2];
-                    acc[4] += u[0] * u[0];
-                    acc[5] += u[1] * u[1];
-                    acc[6] += u[2] * u[2];
-                    acc[7] += u[0] * u[1];
-                    acc[8] += u[0] * u[2];
-                    acc[9] += u[1] * u[2];
-                }
-        for (int k = 0; k < 10; ++k) out[k * Nc + c] = acc[k] * inv;
+        if ((int)threadIdx.x < cells * lanes && c < Nc) {
+            const int X = (int)(c % ncx), Y = (int)((c / ncx) % ncy), Z = (int)(c / ((int64_t)ncx * ncy));
+            for (int dx = threadIdx.x % lanes; dx < fac; dx += lanes)
+                for (int dz = 0; dz < fac; ++dz)
+                    for (int dy = 0; dy < fac; ++dy) {
+                        const int x = X * fac + dx, y = Y * fac + dy, z = Z * fac + dz;
+                        uint32_t mask = 0;
+                        if (B.mask >= 0) mask = a.masks[B.mask + (int64_t)z * B.mplane + y * B.mpitch + x];
+                        if (mask & kSolidBit) continue;
+                        const Links<Q> L = classify<Q>(mask, B, x, y, z, a);
+                        typename Codec<ST>::T f[Q];
+                        gather<Q, ST, SWAPPED>(a, B, cell_off(B, x, y, z), x, y, z, L.bb | L.alo | L.ahi | wrap_bit(a, B, y, z), f);
+                        double drho = 0, j[3] = {0, 0, 0};
+                        sfor<Q>([&](auto I) {
+                            constexpr int i = decltype(I)::value;
+                            const double v = (double)f[i];
+                            drho += v;
+                            if constexpr (cx<Q>(i) != 0) j[0] += cx<Q>(i) * v;
+                            if constexpr (cy<Q>(i) != 0) j[1] += cy<Q>(i) * v;
+                            if constexpr (cz<Q>(i) != 0) j[2] += cz<Q>(i) * v;
+                        });
+                        const double rho = 1.0 + drho;
+                        double u[3];
+                        for (int k = 0; k < 3; ++k) u[k] = (j[k] + 0.5 * a.force[k]) / rho;
+                        acc[0] += rho;
+                        acc[1] += u[0];
+                        acc[2] += u[1];
+                        acc[3] += u[2];
+                        acc[4] += u[0] * u[0];
+                        acc[5] += u[1] * u[1];
+                        acc[6] += u[2] * u[2];
+                        acc[7] += u[0] * u[1];
+                        acc[8] += u[0] * u[2];
+                        acc[9] += u[1] * u[2];
+                    }
+        }
+        for (int k = 0; k < 10; ++k) sum[k][threadIdx.x] = acc[k];
+        __syncthreads();
+        for (int e = threadIdx.x; e < 10 * cells; e += kWG) {
+            const int g = e % cells, k = e / cells;
+            if (c0 + g >= Nc) continue;
+            double r = 0.0;
+            for (int d = 0; d < lanes; ++d) r += sum[k][g * lanes + d];
+            out[k * Nc + c0 + g] = r * inv;
+        }
+        __syncthreads();
     }
 }
 
@@ -2462,8 +2482,9 @@ hipError_t WLB_CAT(pdfs_, WLB_SUFFIX)(int q, const SweepArgs &a, double *buf, in
 hipError_t WLB_CAT(filter_, WLB_SUFFIX)(int q, const SweepArgs &a, int fac, double *out, int64_t ncoarse,
                                         bool swapped, hipStream_t st)
 {
-    int64_t g = (ncoarse + kWG - 1) / kWG;
-    if (g > 16384) g = 16384;
+    const int64_t cells = fac < kWG ? kWG / fac : 1;
+    int64_t g = (ncoarse + cells - 1) / cells;
+    if (g > 65536) g = 65536;
     if (g < 1) g = 1;
     return by_set(q, [&](auto S) {
         constexpr int Q = decltype(S)::value;

@@ -1,5 +1,6 @@
-"""Minibatch sizes around the tiles of the gradient kernel: 32 samples per
-wavefront, 256 per workgroup, more than 512 workgroups' worth in rounds."""
+"""Minibatch sizes and filter factors around the tiles of the training
+kernels: 32 samples per wavefront, 256 per workgroup, more than 512
+workgroups' worth in rounds; one thread per fine x position of a coarse cell."""
 import numpy as np
 import pytest
 import torch
@@ -60,3 +61,34 @@ def test_infinite_target_stays_in_its_own_terms():
     target[5] = float("inf")
     _, loss = _grad(P, raw, target)
     assert loss == float("inf")
+
+
+@pytest.mark.parametrize("fac,cells", [(1, (37, 3, 2)), (3, (23, 2, 5)), (4, (65, 3, 2)), (5, (52, 2, 1)), (130, (2, 1, 1)),
+                                       (257, (1, 1, 1))])
+@pytest.mark.parametrize("steps", [0, 1])
+def test_box_filter_factors(fac, cells, steps):
+    """Averages over factor^3 cells against the library's own per-cell
+    moments: factors that do and do not divide a workgroup, one coarse cell
+    per workgroup, and one wider than a workgroup."""
+    dom = tuple(fac * c for c in cells)
+    say(f"case filter {fac} {dom} steps {steps}")
+    rho, u = inputs.random_state(dom, seed=5, umag=0.01)
+    B = wlb.Blocks(wlb.single_block(dom), dom, (1, 1, 1), stencil=9, storage=wlb.F32)
+    try:
+        B.init(wlb.SRT, wlb.make_params(tau=0.7, force=(1e-5, 0, 0)), rho, u)
+        B.step(steps)
+        r, v, _ = B.moments()
+        nc = cells[0] * cells[1] * cells[2]
+        out = torch.full((10 * nc,), float("nan"), dtype=torch.float64, device="cuda")
+        wlb.wlb_box_filter(B.h, fac, out.data_ptr())
+        got = out.cpu().numpy().reshape(10, nc)
+    finally:
+        B.close()
+
+    def avg(a):
+        return a.reshape(cells[2], fac, cells[1], fac, cells[0], fac).mean(axis=(1, 3, 5)).reshape(-1)
+
+    ref = [avg(r)] + [avg(v[a]) for a in range(3)] + [avg(v[a] * v[b]) for a, b in
+                                                      ((0, 0), (1, 1), (2, 2), (0, 1), (0, 2), (1, 2))]
+    for k in range(10):  # FP64 sums of factor^3 terms of one size
+        assert np.abs(got[k] - ref[k]).max() <= 1e-15 * fac ** 3 * max(1e-30, np.abs(r).max() if k == 0 else 0.02), k
