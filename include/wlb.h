@@ -328,9 +328,9 @@ int wlb_set_lds_staging(wlb_blocks_t h, int32_t on);
  * Errors: WLB_ERR_ARG (null handle), WLB_ERR_HIP (stream creation). */
 int wlb_set_overlap(wlb_blocks_t h, int32_t on);
 
-/* Non-temporal hint (1, default) or ordinary cached accesses (0) for the
- * population loads and stores of the even and of the odd sweep; for the odd
- * sweep also 2: the hint on its aligned accesses only (the populations with
+/* Non-temporal hint (1) or ordinary cached accesses (0) for the population
+ * loads and stores of the even and of the odd sweep (until set here or by the
+ * autotuner: chosen by size and storage type); for the odd sweep also 2: the hint on its aligned accesses only (the populations with
  * c_x = 0, whole lines per wavefront), the others cached.  Streamed once per
  * sweep, the populations usually gain from the hint; accesses one element
  * off the row alignment, and short rows whose cache lines neighbouring waves

@@ -135,8 +135,9 @@ struct wlb_blocks {
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     PinnedRing ring;  // pinned buffers of the host transfers
     bool use_graph = true;
-    hipGraphExec_t gexec = nullptr;
-    hipGraph_t graph = nullptr;
+    // captured step pairs: graphs of one pair and of kGraphPairs pairs
+    hipGraphExec_t gexec[2] = {nullptr, nullptr};
+    hipGraph_t graph[2] = {nullptr, nullptr};
     bool graph_valid = false;
     // kernel timing
     bool timing = false;
@@ -664,28 +665,41 @@ int one_step(wlb_blocks *h)
 
 void drop_graph(wlb_blocks *h)
 {
-    if (h->gexec) hipGraphExecDestroy(h->gexec);
-    if (h->graph) hipGraphDestroy(h->graph);
-    h->gexec = nullptr;
-    h->graph = nullptr;
+    for (int k = 0; k < 2; ++k) {
+        if (h->gexec[k]) hipGraphExecDestroy(h->gexec[k]);
+        if (h->graph[k]) hipGraphDestroy(h->graph[k]);
+        h->gexec[k] = nullptr;
+        h->graph[k] = nullptr;
+    }
     h->graph_valid = false;
 }
 
-int capture_graph(wlb_blocks *h)
+// Step pairs in the longer graph.  A launch of a graph costs the host and the
+// queue some 5-10 us beyond its kernels, which a small box's pair does not
+// hide (32^3 FP64: 16 us per launch of one pair whose kernels take 10 us).
+constexpr int kGraphPairs = 8;
+
+// The graph of one pair (k = 0) or kGraphPairs pairs (k = 1), captured at its
+// first use.
+int capture_graph(wlb_blocks *h, int k)
 {
-    drop_graph(h);
+    if (!h->graph_valid) drop_graph(h);
+    h->graph_valid = true;
+    if (h->gexec[k]) return WLB_OK;
     HIPCHK(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-    const int r1 = enqueue_step(h, false);
-    const int r2 = r1 ? r1 : enqueue_step(h, true);
+    int r = WLB_OK;
+    for (int p = 0; p < (k ? kGraphPairs : 1) && !r; ++p) {
+        r = enqueue_step(h, false);
+        if (!r) r = enqueue_step(h, true);
+    }
     hipGraph_t g = nullptr;
     hipError_t ec = hipStreamEndCapture(h->stream, &g);
-    if (r1 || r2 || ec != hipSuccess) {
+    if (r || ec != hipSuccess) {
         if (g) hipGraphDestroy(g);
         return fail(WLB_ERR_HIP, "graph capture failed: %s", hipGetErrorString(ec != hipSuccess ? ec : hipErrorUnknown));
     }
-    h->graph = g;
-    HIPCHK(hipGraphInstantiate(&h->gexec, g, nullptr, nullptr, 0));
-    h->graph_valid = true;
+    h->graph[k] = g;
+    HIPCHK(hipGraphInstantiate(&h->gexec[k], g, nullptr, nullptr, 0));
     return WLB_OK;
 }
 
@@ -1260,6 +1274,21 @@ int wlb_blocks_create(const wlb_block_desc *d, int32_t n, const int32_t domain[3
     size_t off = 0;
     h->off_pop = off;
     h->pop_bytes = round_up(elems * h->esize, 256);
+    // Cache hints until the caller or the autotuner sets others.  Populations
+    // that fit the 256 MB Infinity Cache gain from staying cached (us per
+    // step, none / both sweeps hinted: 96^3 FP32 28.1 / 34.6, 128^3 FP32 53.7
+    // / 64.4, 96^3 BF16 25.7 / 36.9).  Larger ones stream: hinted even sweep,
+    // and odd sweep hinted on its aligned accesses for FP64 and for FP32 up
+    // to D3Q19 (200^3 FP64: 463, cached 475, all hinted 500; 250x150x190 FP32:
+    // 196, 202, 225), cached otherwise (250x150x190 BF16: 129, aligned only
+    // 138, all 144; 160^3 D3Q27 FP32: 180, 192, 217).
+    if (h->pop_bytes <= (size_t)256 << 20) {
+        h->nt_even = false;
+        h->nt_odd = 0;
+    } else {
+        h->nt_even = true;
+        h->nt_odd = storage == WLB_F64 || (storage == WLB_F32 && stencil <= WLB_D3Q19) ? 2 : 0;
+    }
     off += h->pop_bytes;
     h->off_mask = off;
     h->mask_words = mwords;
@@ -1652,16 +1681,17 @@ int wlb_lbm_step(wlb_blocks_t h, int32_t nsteps)
             if (rc) return rc;
             nsteps -= 1;
         } else {
-            if (!h->graph_valid) {
-                rc = capture_graph(h);
-                if (rc) return rc;
-            }
-            HIPCHK(hipGraphLaunch(h->gexec, h->stream));
+            // the longer graph where no health check is due before its end
+            const int n = 2 * kGraphPairs;
+            const int k = nsteps >= n && (he <= 0 || (h->steps + n - 1) / he == h->steps / he) ? 1 : 0;
+            rc = capture_graph(h, k);
+            if (rc) return rc;
+            HIPCHK(hipGraphLaunch(h->gexec[k], h->stream));
             h->last_wrapped = wraps_in_place(h);
             h->ghost_stale = h->last_wrapped;
             h->last_sweep = 1;
-            h->steps += 2;
-            nsteps -= 2;
+            h->steps += k ? n : 2;
+            nsteps -= k ? n : 2;
         }
         if (he > 0 && (h->steps / he) != (before / he)) {
             rc = health_check(h);

@@ -95,3 +95,48 @@ def test_wrapping_in_place_at_small_extents(nx, ny, nz, q, coll):
             op = oracle_params(q, coll, 0.7, 3 / 16, periodic, F, omega_bulk=1.1)
             do, ro, uo, _ = oracle_run(op, dom, rho, u, None, steps)
             assert pop_err(d, do, q) <= 1e-12 and rel_l2(uu.reshape(3, -1), uo) <= 1e-12, (periodic, steps)
+
+
+@pytest.mark.parametrize("he", [0, 5, 16, 24])
+def test_long_graph_replays_match_eager_steps(he):
+    """Step counts around the longer captured graph (16 steps), replayed with
+    eager work and synchronisations between, and health checks due inside,
+    at the end of and after a replay: bit for bit the eager steps."""
+    say(f"case long graph health {he}")
+    dom = (20, 12, 9)
+    rho, u = inputs.random_state(dom, seed=6, umag=0.01)
+    p = wlb.make_params(tau=0.7, magic=3 / 16, force=(1e-5, 0.0, 1e-6), health_every=he)
+    runs = []
+    for graph in (True, False):
+        B = wlb.Blocks(wlb.single_block(dom), dom, (1, 0, 1), stencil=19, storage=wlb.F64)
+        try:
+            B.init(wlb.TRT, p, rho, u)
+            B.set_graph(graph)
+            out = []
+            for n in (16, 37, 1, 15, 33, 2, 48):
+                B.step(n)
+                out.append(B.pdfs_get())
+                assert B.info().steps == sum((16, 37, 1, 15, 33, 2, 48)[:len(out)])
+            B.set_nontemporal(1, 1)  # drops the captured graphs
+            B.step(34)
+            out.append(B.pdfs_get())
+            runs.append(out)
+        finally:
+            B.close()
+    for k, (a, b) in enumerate(zip(*runs)):
+        assert np.array_equal(a, b), k
+
+
+def test_health_check_stops_a_diverging_run_at_its_step():
+    """A run whose velocity leaves the limit is stopped at the first check due,
+    as with a graph of one pair."""
+    dom = (16, 8, 8)
+    rho, u = inputs.uniform_state(dom, u=(0.2, 0.0, 0.0))
+    B = wlb.Blocks(wlb.single_block(dom), dom, (1, 1, 1), stencil=19, storage=wlb.F64)
+    try:
+        B.init(wlb.TRT, wlb.make_params(tau=0.8, health_every=20, health_umax=0.1), rho, u)
+        with pytest.raises(wlb.WlbError) as e:
+            B.step(100)
+        assert e.value.code == wlb.WLB_ERR_DIVERGED and B.info().steps == 20
+    finally:
+        B.close()
