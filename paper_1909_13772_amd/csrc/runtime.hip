@@ -91,7 +91,12 @@ struct wlb_blocks {
     size_t off_pop = 0, pop_bytes = 0, off_mask = 0, mask_words = 0, off_blocks = 0, off_tiles = 0,
            tile_cap = 0, off_pull = 0, off_push = 0, off_partials = 0, off_totals = 0, off_stage = 0,
            stage_bytes = 0, off_mlp = 0, arena_bytes = 0, off_cells = 0, off_ltiles = 0, ltile_cap = 0,
-           off_vtiles = 0, vtile_cap = 0;
+           off_vtiles = 0, vtile_cap = 0, off_strips = 0;
+    // sweep tiles of 256 consecutive cells over the domain (unified) or over
+    // each x-run: what the whole-row shape means for the direct sweeps
+    std::vector<int4> strips;
+    int strip_row = 0;  // places of a row in the strips (0: none)
+    std::vector<int64_t> run_mask;  // first mask word of each run
     char *arena = nullptr;
     hipStream_t stream = nullptr;
     bool bound = false, inited = false;
@@ -237,6 +242,10 @@ size_t relayout_slots(wlb_blocks *h, size_t round)
         }
         h->dev[h->nblk + r].slot = slot;
         h->dev[h->nblk + r].pop = pop;
+        if (h->unified) {
+            h->dev.back().slot = slot;
+            h->dev.back().pop = 0;
+        }
     }
     h->slot_round = round;
     return elems;
@@ -311,6 +320,40 @@ void update_lds_stride(wlb_blocks *h)
     h->args.vec_odd = (h->vec_want && h->vec_ok && !h->overlap) ? 1 : 0;
     if (h->args.vec_odd) h->args.lds_stride = 0;
     h->graph_valid = false;
+    // tiles of the sweeps.  Whole rows are cut into strips of 256 consecutive
+    // places, which leave few lanes idle whatever the row length (box tiles of
+    // whole rows hold 160 of 256 lanes at rows of 160 cells, 320 of 512 at
+    // 320); the LDS-staged odd sweep and the interior / frontier split need
+    // boxes.
+    SweepArgs &a = h->args;
+    a.strip = 0;
+    if (!h->bound) return;
+    if (h->list_mode) {
+        a.stiles = reinterpret_cast<const int4 *>(h->arena + h->off_ltiles);
+        a.nstiles = (int)h->ltiles.size();
+    } else if (h->shape[0] == 0 && h->run_shape.empty() && !h->overlap && a.lds_stride == 0 && h->strip_row > 0) {
+        a.stiles = reinterpret_cast<const int4 *>(h->arena + h->off_strips);
+        a.nstiles = (int)h->strips.size();
+        a.strip = h->strip_row;
+    } else {
+        a.stiles = a.tiles;
+        a.nstiles = a.ntiles;
+    }
+}
+
+// Strips over one descriptor's cells in x, y, z order, W places per row.
+void strip_region(const DevBlock &D, int b, int64_t W, std::vector<int4> &out)
+{
+    const int64_t n1 = D.n[1], cells = W * n1 * D.n[2];
+    for (int64_t s = 0; s < cells; s += kWG) {
+        const int64_t count = std::min<int64_t>(kWG, cells - s);
+        const int64_t r0 = s / W, r1 = (s + count - 1) / W;  // rows touched
+        const int64_t y0 = r0 % n1, z0 = r0 / n1, y1 = r1 % n1, z1 = r1 / n1;
+        // rows y0 .. y1 of plane z0 = z1, or the end of z0 and the start of z1
+        const bool ylo = y0 == 0 || z1 > z0, yhi = y1 == n1 - 1 || z1 > z0;
+        const bool edge = (D.wylo && ylo) || (D.wyhi && yhi) || (D.wzlo && z0 == 0) || (D.wzhi && z1 == D.n[2] - 1);
+        out.push_back(make_int4(b, (int)(s % W) | (int)(count << 16), (int)y0 | (edge ? kStripEdge : 0), (int)z0));
+    }
 }
 
 // Elements per 16-byte vector of the storage type.
@@ -322,14 +365,15 @@ int build_vtiles(wlb_blocks *h)
 {
     const int V = row_vec(h);
     h->vec_ok = h->params.closure != WLB_CLOSURE_MLP && !h->rhost.empty();
-    for (size_t b = h->nblk; b < h->dev.size() && h->vec_ok; ++b) {
+    const size_t end = h->nblk + h->runs.size();
+    for (size_t b = h->nblk; b < end && h->vec_ok; ++b) {
         const DevBlock &D = h->dev[b];
         const int L = D.n[0] / V;
         if (D.wrapx == 0 || D.mask >= 0 || D.xoff != 0 || D.n[0] % V != 0 || L > kWG || L < 1) h->vec_ok = false;
     }
     h->vtiles.clear();
     if (!h->vec_ok) return WLB_OK;
-    for (size_t b = h->nblk; b < h->dev.size(); ++b) {
+    for (size_t b = h->nblk; b < end; ++b) {
         const DevBlock &D = h->dev[b];
         const int R = kWG / (D.n[0] / V);
         for (int z = 0; z < D.n[2]; ++z)
@@ -360,13 +404,6 @@ int upload_tiles(wlb_blocks *h)
                           hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     h->args.ntiles = (int)h->tiles.size();
-    if (h->list_mode) {
-        h->args.stiles = reinterpret_cast<const int4 *>(h->arena + h->off_ltiles);
-        h->args.nstiles = (int)h->ltiles.size();
-    } else {
-        h->args.stiles = h->args.tiles;
-        h->args.nstiles = h->args.ntiles;
-    }
     update_lds_stride(h);
     return WLB_OK;
 }
@@ -396,7 +433,7 @@ int set_tiles(wlb_blocks *h, int tx, int ty, int tz, int grid)
 
 int launch_grid(const wlb_blocks *h)
 {
-    const int n = (int)(h->list_mode ? h->ltiles.size() : h->tiles.size());
+    const int n = h->args.nstiles;
     if (h->grid <= 0 || h->grid > n) return n > 0 ? n : 1;
     return h->grid;
 }
@@ -862,7 +899,7 @@ int autotune(wlb_blocks *h)
             for (int g : kGrids) {
                 int rc = set_tiles(h, s[0], s[1], s[2], g);
                 if (rc) return rc;
-                if (g > 0 && g >= (int)h->tiles.size()) continue;  // same as one workgroup per tile
+                if (g > 0 && g >= h->args.nstiles) continue;  // same as one workgroup per tile
                 if (lds == 1 && h->args.lds_stride == 0) continue;  // staging does not fit: covered by lds = 0
                 if (lds == 2 && !h->args.vec_odd) continue;
                 float ms = 0.f;
@@ -1249,9 +1286,11 @@ int wlb_blocks_create(const wlb_block_desc *d, int32_t n, const int32_t domain[3
         R.nbx[0] = h->dev[r.front()].nbx[0];
         R.nbx[1] = h->dev[r.back()].nbx[1];
         R.mpitch = (int32_t)round_up(W, 32);
-        R.mplane = R.mpitch * F.n[1];
-        R.mask = (int64_t)mwords;  // provisional; -1 if the run has no solid nearby (set at init)
-        mwords += (size_t)R.mplane * F.n[2];
+        R.mplane = R.mpitch * ny;
+        // provisional; -1 if the run has no solid nearby (set at init)
+        R.mask = h->unified ? (int64_t)F.org[2] * R.mplane + (int64_t)F.org[1] * R.mpitch : (int64_t)mwords;
+        mwords = h->unified ? (size_t)R.mplane * nz : mwords + (size_t)R.mplane * nz;
+        h->run_mask.push_back(R.mask);
         for (int m : r) {
             DevBlock &D = h->dev[m];
             D.mpitch = R.mpitch;
@@ -1270,6 +1309,17 @@ int wlb_blocks_create(const wlb_block_desc *d, int32_t n, const int32_t domain[3
         h->rhost.push_back(RH);
     }
     h->dev.insert(h->dev.end(), rdev.begin(), rdev.end());
+    if (h->unified) {  // the domain as one block, for the strips
+        DevBlock D = h->dev[n];
+        for (int a = 0; a < 3; ++a) {
+            D.n[a] = domain[a];
+            D.g[a] = 0;
+        }
+        D.mask = 0;
+        D.wylo = D.wyhi = h->periodic[1] ? domain[1] * D.pitch : 0;
+        D.wzlo = D.wzhi = h->periodic[2] ? domain[2] * D.plane : 0;
+        h->dev.push_back(D);
+    }
     elems = relayout_slots(h, kSlotRoundMax);
     size_t off = 0;
     h->off_pop = off;
@@ -1285,6 +1335,13 @@ int wlb_blocks_create(const wlb_block_desc *d, int32_t n, const int32_t domain[3
     if (h->pop_bytes <= (size_t)256 << 20) {
         h->nt_even = false;
         h->nt_odd = 0;
+        // one contiguous range of tiles per XCD, whose L2 then serves the
+        // shifted accesses of neighbouring rows (us per step, against tiles
+        // dealt out in turn: 130 x 90 x 100 FP32 34.8 / 36.4, 110 x 180 x 180
+        // FP16 59.4 / 67.4, 40 x 90 x 100 FP32 11.9 / 13.5; streaming domains
+        // lose by it: 256^3 FP32 461 / 435)
+        h->grid = -1;
+        h->args.xcd_map = 1;
     } else {
         h->nt_even = true;
         h->nt_odd = storage == WLB_F64 || (storage == WLB_F32 && stencil <= WLB_D3Q19) ? 2 : 0;
@@ -1317,6 +1374,20 @@ int wlb_blocks_create(const wlb_block_desc *d, int32_t n, const int32_t domain[3
     for (const HostBlock &B : h->rhost) h->vtile_cap += (size_t)B.n[1] * B.n[2];
     h->off_vtiles = off;
     off += round_up(h->vtile_cap * sizeof(int4), 256);
+    // Rows of whole lines (256 bytes and more) count their last line in full,
+    // so that no line is shared by two wavefronts (us per step: 250 x 150 x 190
+    // BF16 118, with 250 places per row 171; FP32 190 and 278; a row per box
+    // tile 122 and 190, and where that leaves lanes idle 320^3 FP16 675 against
+    // 558, 160^3 D3Q27 KBC FP32 258 against 195, 170^3 BF16 104 against 91).
+    bool same_rows = true;
+    for (const HostBlock &B : h->rhost) same_rows = same_rows && B.n[0] == domain[0];
+    if (same_rows) {
+        h->strip_row = (size_t)domain[0] * h->esize >= 256 ? (int)round_up(domain[0], align_e) : domain[0];
+        for (int b = h->unified ? n + (int)runs.size() : n; b < (int)h->dev.size(); ++b)
+            strip_region(h->dev[b], b, h->strip_row, h->strips);
+    }
+    h->off_strips = off;
+    off += round_up(h->strips.size() * sizeof(int4), 256);
     // --- exchange work lists
     // Items of one y/z face (or edge) direction k of descriptor a (extent
     // and neighbour flags A) with neighbour descriptor nbd (extent Bn).
@@ -1462,6 +1533,8 @@ int wlb_blocks_bind(wlb_blocks_t h, void *arena, size_t bytes, void *stream)
     h->stream = static_cast<hipStream_t>(stream);
     drop_graph(h);
     HIPCHK(hipMemsetAsync(h->arena, 0, h->off_blocks, h->stream));  // populations and masks
+    HIPCHK(hipMemcpyAsync(h->arena + h->off_strips, h->strips.data(), h->strips.size() * sizeof(int4),
+                          hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemcpyAsync(h->arena + h->off_pull, h->pull.data(), h->pull.size() * sizeof(XItem),
                           hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemcpyAsync(h->arena + h->off_push, h->push.data(), h->push.size() * sizeof(XItem),
@@ -1534,7 +1607,7 @@ int wlb_lbm_init(wlb_blocks_t h, int32_t collision, const wlb_lbm_params *p, con
     if (solid)
         for (int64_t k = 0; k < N; ++k) nsolid += solid[k] ? 1 : 0;
     h->nfluid = N - nsolid;
-    int64_t mwords = 0;
+    bool any_mask = false;
     for (size_t r = 0; r < h->rhost.size(); ++r) {
         const HostBlock &B = h->rhost[r];
         DevBlock &D = h->dev[h->nblk + r];
@@ -1555,10 +1628,16 @@ int wlb_lbm_init(wlb_blocks_t h, int32_t collision, const wlb_lbm_params *p, con
                         if (ok && solid[(g[2] * (int64_t)h->dom[1] + g[1]) * h->dom[0] + g[0]]) need = true;
                     }
         }
-        D.mask = need ? mwords : -1;
-        mwords += (int64_t)D.mplane * B.n[2];
+        D.mask = need ? h->run_mask[r] : -1;
+        any_mask = any_mask || need;
         for (int m : h->runs[r])
             h->dev[m].mask = need ? D.mask + (h->blocks[m].org[0] - B.org[0]) : -1;
+    }
+    if (h->unified) {
+        // the domain's strips read the masks of every run, also of those
+        // without solids: clear what an earlier geometry left
+        h->dev.back().mask = any_mask ? 0 : -1;
+        if (any_mask) HIPCHK(hipMemsetAsync(h->arena + h->off_mask, 0, h->mask_words * 4, h->stream));
     }
     HIPCHK(hipMemcpyAsync(h->arena + h->off_blocks, h->dev.data(), h->dev.size() * sizeof(DevBlock),
                           hipMemcpyHostToDevice, h->stream));
@@ -1828,7 +1907,7 @@ int wlb_info(wlb_blocks_t h, wlb_info_t *o)
     o->n_blocks = (int32_t)h->blocks.size();
     o->n_cells = h->ncells;
     o->n_fluid = h->inited ? h->nfluid : h->ncells;
-    o->n_tiles = (int32_t)(h->list_mode ? h->ltiles.size() : h->tiles.size());
+    o->n_tiles = h->bound ? h->args.nstiles : (int32_t)h->tiles.size();
     for (int a = 0; a < 3; ++a) o->tile[a] = h->shape[a];
     {
         std::vector<int> cls;

@@ -734,10 +734,15 @@ __device__ __forceinline__ void cumulant_collide(T (&d)[Q], const Macro<Q, T> &m
     });
 }
 
-template <typename T>
+// CL: the closure when known at compile time (0: none), -1: read from the
+// arguments.  A sweep without a closure compiled apart from the Smagorinsky
+// branch keeps 10-20 vector registers fewer (FP16 odd sweep: no spills, 357
+// -> 330 us on the 256^3 channel; D3Q27 MRT FP32 at 160^3: 204 -> 194 us).
+template <typename T, int CL = -1>
 struct CollParams {
     T om, omm, magic, omb, omh, F[3], tau0, smag_k;
-    int closure;
+    int closure_arg;
+    __device__ __forceinline__ int closure() const { return CL >= 0 ? CL : closure_arg; }
 };
 
 // Uniform value the compiler may not treat as loop-invariant: the parameters
@@ -751,10 +756,10 @@ __device__ __forceinline__ double opaque(double v)
     return v;
 }
 
-template <typename T>
-__device__ __forceinline__ CollParams<T> coll_params(const SweepArgs &a)
+template <typename T, int CL = -1>
+__device__ __forceinline__ CollParams<T, CL> coll_params(const SweepArgs &a)
 {
-    CollParams<T> c;
+    CollParams<T, CL> c;
     c.om = (T)opaque(a.omega);
     c.omm = (T)opaque(a.omega_minus);
     c.magic = (T)opaque(a.magic);
@@ -765,7 +770,7 @@ __device__ __forceinline__ CollParams<T> coll_params(const SweepArgs &a)
     c.F[2] = (T)opaque(a.force[2]);
     c.tau0 = (T)opaque(a.tau0);
     c.smag_k = (T)opaque(a.smag_k);
-    c.closure = a.closure;
+    c.closure_arg = a.closure;
     return c;
 }
 
@@ -920,22 +925,22 @@ __device__ __forceinline__ void relax_pairs(T (&d)[Q], const Macro<Q, T> &m, con
 }
 
 // Collide one cell in place.  Returns the macroscopic state used.
-template <int Q, int COLL, typename T, typename A = T>
-__device__ __forceinline__ Macro<Q, T> collide(T (&d)[Q], const CollParams<T> &p)
+template <int Q, int COLL, typename T, typename A = T, int CL = -1>
+__device__ __forceinline__ Macro<Q, T> collide(T (&d)[Q], const CollParams<T, CL> &p)
 {
     const Macro<Q, T> m = moments_of<Q, T>(d, p.F);
     T om = p.om, omm = p.omm;
     if constexpr (COLL == 4) {
-        if (p.closure == 1) {
+        if (p.closure() == 1) {
             T P[6];
             pi_pairs<Q, T>(d, m, P);
             om = recip(tau_smagorinsky<T>(P, m.rho, p.tau0, p.smag_k));
         }
         cumulant_collide<Q, T>(d, m, p.F, om, p.omb);
     } else if constexpr (COLL == 2 || COLL == 3) {
-        mrt_collide<Q, T, COLL == 3, A>(d, m, p.F, om, p.omb, p.omh, p.closure, p.tau0, p.smag_k);
+        mrt_collide<Q, T, COLL == 3, A>(d, m, p.F, om, p.omb, p.omh, p.closure(), p.tau0, p.smag_k);
     } else {
-        if (p.closure == 1) {
+        if (p.closure() == 1) {
             T P[6];
             pi_pairs<Q, T>(d, m, P);
             const T tau = tau_smagorinsky<T>(P, m.rho, p.tau0, p.smag_k);
@@ -985,10 +990,30 @@ __device__ __forceinline__ CellPos tile_cell(const int4 tv, int l)
     return c;
 }
 
-// Cell of lane l in a sweep tile: a box tile, or a list tile of fluid cells
-// (porous media: no lanes spent on solid cells, full waves on short rows).
-__device__ __forceinline__ CellPos sweep_cell(const SweepArgs &a, const int4 tv, int l)
+// Quotient v / n of small non-negative integers: (v + 1/2) / n lies at least
+// 1 / (2 n) from a whole number, the FP32 product with the 1-ulp reciprocal
+// within (v + 1) / n 2^-22 of it, so the truncation is exact for v < 2^20.
+__device__ __forceinline__ int small_div(int v, int n)
 {
+    return (int)(((float)v + 0.5f) * __builtin_amdgcn_rcpf((float)n));
+}
+
+// Cell of lane l in a sweep tile of descriptor B: a strip of consecutive
+// cells (every lane has one, whatever the row length, and no integer
+// division), a box tile, or a list tile of fluid cells (porous media: no lanes
+// spent on solid cells).
+__device__ __forceinline__ CellPos sweep_cell(const SweepArgs &a, const DevBlock &B, const int4 tv, int l)
+{
+    if (a.strip) {
+        CellPos c;
+        const int x = (tv.y & 0xffff) + l, kx = small_div(x, a.strip);
+        const int y = (tv.z & 0xffff) + kx, ky = small_div(y, B.n[1]);
+        c.x = x - kx * a.strip;
+        c.valid = l < (tv.y >> 16) && c.x < B.n[0];
+        c.y = y - ky * B.n[1];
+        c.z = tv.w + ky;
+        return c;
+    }
     if (tv.w >= 0) return tile_cell(tv, l);
     CellPos c;
     c.valid = l < -tv.w;
@@ -1177,7 +1202,7 @@ __device__ __forceinline__ uint32_t wrap_bit(const SweepArgs &a, const DevBlock 
 __device__ __forceinline__ uint32_t wrap_bit(const SweepArgs &a, const DevBlock &B, const int4 tv, int y, int z)
 {
     const int y0 = tv.z & 0xffff, z0 = tv.w & 0xffff;
-    const bool tile = tv.w < 0 || (B.wylo && y0 == 0) || (B.wyhi && y0 + (tv.z >> 16) == B.n[1]) || (B.wzlo && z0 == 0) ||
+    const bool tile = a.strip ? (tv.z & kStripEdge) != 0 : tv.w < 0 || (B.wylo && y0 == 0) || (B.wyhi && y0 + (tv.z >> 16) == B.n[1]) || (B.wzlo && z0 == 0) ||
                       (B.wzhi && z0 + (tv.w >> 16) == B.n[2]);
     return tile ? wrap_bit(a, B, y, z) : 0u;
 }
@@ -1416,22 +1441,30 @@ __device__ __forceinline__ void store_regular_out(const SweepArgs &a, const DevB
 // ---------------------------------------------------------------------------
 // The sweep kernel (one launch covers every tile of every block)
 // ---------------------------------------------------------------------------
-#ifndef WLB_WAVES_PER_EU
-#define WLB_WAVES_PER_EU 1
-#endif
+// Wavefronts per SIMD of a direct sweep.  At least 6 for the 16-bit sweeps up
+// to D3Q19 (at most 80 VGPRs): they are bound by vector instructions and
+// latency, which the extra wavefronts hide (256^3 channel: FP16 48.9k ->
+// 51.3k MLUPS); D3Q27 spills there and takes the compiler's own allocation.
+// At most 3 for the FP64 even sweep up to D3Q19: bound by its accesses, it
+// gains nothing from a fourth and loses order in memory (256^3 channel 897 ->
+// 873 us, 200^3 468 -> 447 us).  Elsewhere the compiler's own allocation.
+template <int Q, typename ST>
+constexpr int kWavesMin = (kStochastic<ST> && Q <= 19) ? 6 : 1;
+template <int Q, typename ST, bool ODD>
+constexpr int kWavesMax = (std::is_same_v<ST, double> && Q <= 19 && !ODD) ? 3 : 8;
 // NT: the population accesses carry the non-temporal hint (the autotuner
 // chooses it per parity).
 // AO: the odd sweep's hint on its aligned accesses only (nt_shifted).
-template <int Q, int COLL, typename ST, bool ODD, bool NT, bool AO>
+template <int Q, int COLL, typename ST, bool ODD, bool NT, bool AO, int CL>
 __device__ __forceinline__ void sweep_tiles(const SweepArgs &a)
 {
     using T = typename Codec<ST>::T;
     for (int t = first_tile(a); t < a.nstiles; t += gridDim.x) {
-        const CollParams<T> cp = coll_params<T>(a);
+        const CollParams<T, CL> cp = coll_params<T, CL>(a);
         const int4 tv = a.stiles[t];
-        const CellPos c = sweep_cell(a, tv, threadIdx.x);
-        if (!c.valid) continue;
         const DevBlock B = a.blocks[tv.x];
+        const CellPos c = sweep_cell(a, B, tv, threadIdx.x);
+        if (!c.valid) continue;
         uint32_t mask = 0;
         if (B.mask >= 0) mask = a.masks[B.mask + (int64_t)c.z * B.mplane + c.y * B.mpitch + c.x];
         // The even sweep loads and stores a solid cell's slots along with the
@@ -1450,7 +1483,7 @@ __device__ __forceinline__ void sweep_tiles(const SweepArgs &a)
         gather<Q, ST, ODD, NT, AO>(a, B, off, c.x, c.y, c.z, special, f);
         const uint32_t h = kStochastic<ST> ? state_hash<Q, T>(f, global_cell(a, B, c.x, c.y, c.z)) : 0u;
         if (!solid) {
-            const Macro<Q, T> m = collide<Q, COLL, T, AccOf<ST>>(f, cp);
+            const Macro<Q, T> m = collide<Q, COLL, T, AccOf<ST>, CL>(f, cp);
             if (L.alo | L.ahi) {
                 const T rin = (T)a.rho_in, rout = (T)a.rho_out;
                 const T drin = (T)(a.rho_in - 1.0), drout = (T)(a.rho_out - 1.0);
@@ -1477,21 +1510,21 @@ __device__ __forceinline__ void sweep_tiles(const SweepArgs &a)
     }
 }
 
-template <int Q, int COLL, typename ST, bool ODD, bool NT>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WLB_WAVES_PER_EU, 8))) void sweep_kernel(
-    const SweepArgs a)
+template <int Q, int COLL, typename ST, bool ODD, bool NT, int CL>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(kWavesMin<Q, ST>, kWavesMax<Q, ST, ODD>))) void
+sweep_kernel(const SweepArgs a)
 {
-    sweep_tiles<Q, COLL, ST, ODD, NT, false>(a);
+    sweep_tiles<Q, COLL, ST, ODD, NT, false, CL>(a);
 }
 
 // Odd sweep with the non-temporal hint on its aligned accesses only (the
 // populations with c_x = 0); an autotuner candidate beside the odd sweep
 // with the hint on every access and the one without it.
-template <int Q, int COLL, typename ST>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(WLB_WAVES_PER_EU, 8))) void sweep_odd_aligned_nt_kernel(
-    const SweepArgs a)
+template <int Q, int COLL, typename ST, int CL>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(kWavesMin<Q, ST>, kWavesMax<Q, ST, true>))) void
+sweep_odd_aligned_nt_kernel(const SweepArgs a)
 {
-    sweep_tiles<Q, COLL, ST, true, true, true>(a);
+    sweep_tiles<Q, COLL, ST, true, true, true, CL>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1903,8 +1936,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     const MlpDev *net = &net_s;
     for (int t = first_tile(a); t < a.nstiles; t += gridDim.x) {
         const int4 tv = a.stiles[t];
-        const CellPos c = sweep_cell(a, tv, threadIdx.x);
         const DevBlock B = a.blocks[tv.x];
+        const CellPos c = sweep_cell(a, B, tv, threadIdx.x);
         uint32_t mask = 0;
         if (c.valid && B.mask >= 0) mask = a.masks[B.mask + (int64_t)c.z * B.mplane + c.y * B.mpitch + c.x];
         const bool active = c.valid && !(mask & kSolidBit);
@@ -2314,6 +2347,22 @@ __global__ __launch_bounds__(kWG) void force_kernel(const SweepArgs a, double *p
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+template <int Q, int COLL, bool NT, int CL>
+static hipError_t sweep_direct(bool odd, const SweepArgs &a, int grid, hipStream_t st)
+{
+    if constexpr (NT && !std::is_same_v<WLB_STORAGE, cover_t>) {
+        if (odd && a.nt == 2) {  // the hint on the aligned accesses only
+            hipLaunchKernelGGL((sweep_odd_aligned_nt_kernel<Q, COLL, WLB_STORAGE, CL>), dim3(grid), dim3(kWG), 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    if (odd)
+        hipLaunchKernelGGL((sweep_kernel<Q, COLL, WLB_STORAGE, true, NT, CL>), dim3(grid), dim3(kWG), 0, st, a);
+    else
+        hipLaunchKernelGGL((sweep_kernel<Q, COLL, WLB_STORAGE, false, NT, CL>), dim3(grid), dim3(kWG), 0, st, a);
+    return hipGetLastError();
+}
+
 template <int Q, int COLL, bool NT>
 static hipError_t sweep_qn(bool odd, const SweepArgs &a, int grid, hipStream_t st)
 {
@@ -2339,17 +2388,10 @@ static hipError_t sweep_qn(bool odd, const SweepArgs &a, int grid, hipStream_t s
                                a);
         return hipGetLastError();
     }
-    if constexpr (NT && !std::is_same_v<WLB_STORAGE, cover_t>) {
-        if (odd && a.nt == 2) {  // the hint on the aligned accesses only
-            hipLaunchKernelGGL((sweep_odd_aligned_nt_kernel<Q, COLL, WLB_STORAGE>), dim3(grid), dim3(kWG), 0, st, a);
-            return hipGetLastError();
-        }
-    }
-    if (odd)
-        hipLaunchKernelGGL((sweep_kernel<Q, COLL, WLB_STORAGE, true, NT>), dim3(grid), dim3(kWG), 0, st, a);
-    else
-        hipLaunchKernelGGL((sweep_kernel<Q, COLL, WLB_STORAGE, false, NT>), dim3(grid), dim3(kWG), 0, st, a);
-    return hipGetLastError();
+    // the counting storage of the write-coverage check needs one variant only
+    if (a.closure == 0 && !std::is_same_v<WLB_STORAGE, cover_t>)
+        return sweep_direct<Q, COLL, NT, std::is_same_v<WLB_STORAGE, cover_t> ? -1 : 0>(odd, a, grid, st);
+    return sweep_direct<Q, COLL, NT, -1>(odd, a, grid, st);
 }
 
 template <int Q, int COLL>

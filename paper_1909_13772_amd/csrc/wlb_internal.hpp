@@ -65,7 +65,10 @@ static_assert(sizeof(DevBlock) == 112, "DevBlock layout");
 // One tile of a sweep: block id and start/extent (extent <= 256 cells).
 // Packed as int4 {block, x0 | ex << 16, y0 | ey << 16, z0 | ez << 16}.  A
 // list tile (sweeps only) is {block, first entry in the cell list, 0, -count}
-// with up to 256 fluid cells of the block.
+// with up to 256 fluid cells of the block.  A strip (SweepArgs::strip, sweeps
+// only) is up to 256 consecutive cells of a descriptor in x, y, z order: {block,
+// x0 | count << 16, y0 | kStripEdge, z0}.
+constexpr int kStripEdge = 1 << 30;  // the strip touches a face that wraps in place
 struct TileHost {
     int32_t b, x0, y0, z0, ex, ey, ez;
 };
@@ -108,6 +111,7 @@ struct SweepArgs {
     int32_t closure;
     int32_t lds_stride;    // > 0: odd sweep stages x-shifted populations in LDS rows of this many elements
     int32_t lds_ring;      // 1: every tile is a whole row of a self-wrapping block (staged sweep without halos)
+    int32_t strip;         // > 0: stiles are strips over rows of this many places
     int32_t xcd_map;       // 1: one workgroup per tile, each XCD takes a contiguous range of tiles
     int32_t nt;            // 1: the sweep's population accesses carry the non-temporal hint; 2 (odd
                            // sweep): only its aligned ones (populations with c_x = 0)
