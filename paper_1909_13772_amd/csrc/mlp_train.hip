@@ -49,6 +49,46 @@ __device__ __forceinline__ Split3 split3(float x)
     return r;
 }
 
+// Whether an FP32 activation lies within 8 units in the last place of a bf16
+// rounding boundary: its FP32 error (some 3e-7 relative) may then put it on
+// the other side, which changes the bf16 operand by 2^-8.
+__device__ __forceinline__ bool near_boundary(float g)
+{
+    return ((__float_as_uint(g) & 0xffffu) - (0x8000u - 8u)) <= 16u;
+}
+// GELU in FP64 to 1.5e-9, rounded to bf16 through FP32.  erfc(u) = t
+// exp(-u^2 + P(2 t - 1)), t = 1 / (1 + u / 2), the form that half_erfc_parts
+// uses, with P the degree-13 Chebyshev interpolant of log(erfc(u) exp(u^2) / t)
+// on 0 < t <= 1 (largest deviation 1.2e-9); exp by 2^k times the Taylor sum of
+// the remainder to degree 8 (2e-10).
+__device__ __noinline__ __bf16 gelu_bf16(double z)
+{
+    const double u = fabs(z) * 0.70710678118654752440;
+    const double t = 1.0 / fma(0.5, u, 1.0), s = fma(2.0, t, -1.0);
+    constexpr double c[14] = {-0.6717940851517218,     0.6726432205460087,      0.04734341752106161,
+                              -0.046895482161005086,   -0.0098745349182224,     0.008823558177735913,
+                              0.001770666118369054,    -0.002339277724317185,   -0.00018278214127144218,
+                              0.0006579538480657341,   -3.211377267356806e-05,  -0.0001546337909289383,
+                              1.3371503605768667e-05,  2.0723070945002116e-05};
+    double p = c[13];
+#pragma unroll
+    for (int k = 12; k >= 0; --k) p = fma(p, s, c[k]);
+    const double x = fmax(fma(-u, u, p), -700.0);
+    const double k = rint(x * 1.4426950408889634);
+    const double r = fma(-k, 0.6931471805599453, x);
+    double e = 1.0 / 40320.0;
+    e = fma(e, r, 1.0 / 5040.0);
+    e = fma(e, r, 1.0 / 720.0);
+    e = fma(e, r, 1.0 / 120.0);
+    e = fma(e, r, 1.0 / 24.0);
+    e = fma(e, r, 1.0 / 6.0);
+    e = fma(e, r, 0.5);
+    e = fma(e, r, 1.0);
+    e = fma(e, r, 1.0);
+    const double tail = z * (0.5 * t * ldexp(e, (int)k));  // z Phi(-|z|)
+    return (__bf16)(float)(z >= 0.0 ? z - tail : tail);
+}
+
 constexpr int kGradWG = 512;        // eight wavefronts, each one tile of 32 samples at a time
 constexpr int kGradWaves = kGradWG / 64;
 constexpr int kTileS = 32;          // samples of a wavefront's tile
@@ -75,6 +115,11 @@ __device__ __forceinline__ bf16x8_t row8(const bf16row_t &r, int s) { return *re
 // samples: both operands are turned through LDS (rows of one quantity, 32
 // samples) and summed over all of a wavefront's tiles in the accumulators of
 // dW2 = gz2^T h1, dW1 and db1 = gz1^T [x | 1], db2 = gz2^T [x | 1], dw3 = h2^T go.
+//
+// The bf16 operands h1 and h2 are decided in FP64 where the FP32 activation
+// lies next to a rounding boundary (about one in 3,900): the few that FP32
+// decides the other way were most of the gradient's error against FP64 (6e-7
+// to 1.6e-6 of its norm for 16,384 samples, as with one sample per thread).
 //
 // What bounds it: the activations (GELU and its slope, 64 per sample) on the
 // vector ALUs, some 1,700 instructions per tile against 23 matrix products of
@@ -128,38 +173,76 @@ __global__ __launch_bounds__(kGradWG) void mlp_grad_kernel(const float *__restri
             xb[k] = (__bf16)((r - sw[kOffMean + k + zo]) * sw[kOffIstd + k + zo]);
         }
         xb[7] = (__bf16)0.f;
+        if (h == 0) {
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) T[kRowX + k][m] = xb[k];
+            T[kRowX + kIn][m] = (__bf16)1.f;
+        }
         f32x16_t z;
 #pragma unroll
         for (int j = 0; j < 16; ++j) z[j] = sv[kOffB1 + mlp_unit(j, 0)];
         z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, h == 0 ? xb : zero, z, 0, 0, 0);
         float s1[16];  // slopes of layer 1
         bf16x8_t hb[2];
+        uint32_t near = 0;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             float g;
             gelu_and_slope(z[j], g, s1[j]);
             hb[j / 8][j % 8] = (__bf16)g;
             T[kRowH1 + mlp_unit(j, h)][m] = (__bf16)g;
+            near |= act && near_boundary(g) ? 1u << j : 0u;
             // a few activations at a time: all sixteen in flight spill
             if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
+        __syncthreads();
+        if (__any(near != 0)) {
+#pragma unroll 1
+            while (near) {
+                const int u = mlp_unit(__builtin_ctz(near), h);
+                double zd = sw[kOffB1 + u];
+#pragma unroll 1
+                for (int k = 0; k < kIn; ++k)
+                    zd = fma((double)bf16_round(sw[kOffW1 + u * kIn + k]), (double)(float)T[kRowX + k][m], zd);
+                T[kRowH1 + u][m] = gelu_bf16(zd);
+                near &= near - 1;
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) hb[j / 8][j % 8] = T[kRowH1 + mlp_unit(j, h)][m];
+        }
+        __syncthreads();
 #pragma unroll
         for (int j = 0; j < 16; ++j) z[j] = sv[kOffB2 + mlp_unit(j, 0)];
 #pragma unroll
         for (int q = 0; q < 2; ++q) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2[q], hb[q], z, 0, 0, 0);
         float gz[16];  // w3 times the slope of layer 2
-        float o = 0.f;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const float w3 = bf16_round(sv[kOffW3 + mlp_unit(j, 0)]);
             float g, sl;
             gelu_and_slope(z[j], g, sl);
-            const __bf16 b = (__bf16)g;
-            T[kRowH2 + mlp_unit(j, h)][m] = b;
-            o = fmaf(w3, (float)b, o);
-            gz[j] = w3 * sl;
+            hb[j / 8][j % 8] = (__bf16)g;
+            T[kRowH2 + mlp_unit(j, h)][m] = (__bf16)g;
+            near |= act && near_boundary(g) ? 1u << j : 0u;
+            gz[j] = bf16_round(sv[kOffW3 + mlp_unit(j, 0)]) * sl;
             if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
+        if (__any(near != 0)) {
+#pragma unroll 1
+            while (near) {
+                const int u = mlp_unit(__builtin_ctz(near), h);
+                double zd = sw[kOffB2 + u];
+#pragma unroll 2
+                for (int k = 0; k < kH; ++k)
+                    zd = fma((double)bf16_round(sw[kOffW2 + u * kH + k]), (double)(float)T[kRowH1 + k][m], zd);
+                T[kRowH2 + u][m] = gelu_bf16(zd);
+                near &= near - 1;
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) hb[j / 8][j % 8] = T[kRowH2 + mlp_unit(j, h)][m];
+        }
+        float o = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o = fmaf(bf16_round(sv[kOffW3 + mlp_unit(j, 0)]), (float)hb[j / 8][j % 8], o);
         o += __shfl_xor(o, 32, 64);  // the other half of the units
         o += sw[kOffB3];
         // ---- backward
@@ -171,9 +254,6 @@ __global__ __launch_bounds__(kGradWG) void mlp_grad_kernel(const float *__restri
             const Split3 g3 = split3(go);
 #pragma unroll
             for (int p = 0; p < 3; ++p) T[kRowGo + p][m] = g3.p[p];
-#pragma unroll
-            for (int k = 0; k < kIn; ++k) T[kRowX + k][m] = xb[k];
-            T[kRowX + kIn][m] = (__bf16)1.f;
         }
         bf16x8_t gb[3][2];
 #pragma unroll
