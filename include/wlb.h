@@ -250,8 +250,8 @@ typedef struct {
     int32_t n_class_tiles;  /* classes of x-runs (by y extent) whose tile shape the autotuner
                                set apart from `tile` (0: one shape for every run) */
     int32_t slot_round_kib; /* population slots of 64 MiB or more start on multiples of this
-                               many KiB (0: 256-byte alignment only); chosen by the autotuner,
-                               16384 otherwise */
+                               many KiB (0: 256-byte alignment only; 1028: multiples of 1 MiB
+                               plus 4 KiB); chosen by the autotuner, 16384 otherwise */
 } wlb_info_t;
 int wlb_info(wlb_blocks_t h, wlb_info_t *out);
 
@@ -283,7 +283,9 @@ int wlb_set_class_tiles(wlb_blocks_t h, int32_t y_extent, int32_t tx, int32_t ty
 
 /* Slot stride of the population storage (Sec. 4.2: the layout of the
  * fields): slots of 64 MiB or more start on multiples of `kib` KiB (16384,
- * 2048, or 0 = 256-byte alignment only); smaller slots are only aligned.
+ * 2048, or 0 = 256-byte alignment only); smaller slots keep their own
+ * stride (with 16384, slots of 16 MiB or more a multiple of 1 MiB plus 4 KiB,
+ * otherwise alignment only).
  * The arena is sized for 16384, the default.  Call after wlb_blocks_bind and
  * before wlb_lbm_init; an init with the autotuner chooses the stride again.
  * Results do not depend on it.

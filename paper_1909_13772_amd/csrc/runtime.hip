@@ -210,24 +210,39 @@ void tile_region(const HostBlock &B, int b, int tx, int ty, int tz, int y0, int 
             }
 }
 
-// Largest slot stride rounding the autotuner tries: the arena is sized for it.
+// Slot strides.  The sweeps stream all q slots at the same cell offset at
+// once, and on MI355X the achieved bandwidth of that access pattern depends on
+// the slots' stride, not monotonically (stand-alone even pattern over a 256^3
+// FP64 block: 0.82 ms at a 128 MiB stride, 0.96 ms at 129 MiB, 0.83 ms at 130
+// MiB and at 144 MiB).  Slots of 64 MiB or more are rounded up to a multiple
+// of `round` bytes (16 MiB, 2 MiB; 0: alignment only) or skewed: rounded to 1
+// MiB plus 4 KiB; the autotuner chooses by measurement, and the arena is
+// sized for 16 MiB.  Slots of 16 to 64 MiB are skewed, unless the autotuner
+// finds alignment alone faster (us per step, aligned only / skewed: 256^3 FP16
+// 307 / 277, 160^3 FP64 217 / 205, 200^3 FP32 240 / 235, 160 x 216 x 200 porous
+// D3Q27 FP32 334 / 322; at worst 320 x 320 x 180 FP16 310 / 314).  Smaller slots
+// are only aligned.
 constexpr size_t kSlotRoundMax = (size_t)16 << 20;
+constexpr size_t kSlotSkew = ((size_t)1 << 20) + 4096;
 
-// Places the population slots of every x-run one after the other.  The
-// sweeps stream all q slots at the same cell offset at once, and on MI355X
-// the achieved bandwidth of that access pattern depends on the slots'
-// stride, not monotonically (stand-alone even pattern over a 256^3 FP64
-// block: 0.82 ms at a 128 MiB stride, 0.96 ms at 129 MiB, 0.83 ms at 130
-// MiB and at 144 MiB).  Slots of 64 MiB or more are therefore rounded up to
-// a multiple of `round` bytes (0: alignment only), which the autotuner
-// chooses by measurement; smaller slots are only aligned.  Sets pop and
+size_t slot_stride(size_t bytes, size_t round)
+{
+    if (bytes < (size_t)16 << 20) return bytes;
+    const size_t skew = round_up(bytes, (size_t)1 << 20) + 4096;
+    if (bytes < (size_t)64 << 20) return (round == kSlotRoundMax || round == kSlotSkew) ? skew : bytes;
+    if (round == kSlotSkew) return std::min(skew, round_up(bytes, kSlotRoundMax));
+    return round ? round_up(bytes, round) : bytes;
+}
+
+// Places the population slots of every x-run one after the other (of the
+// domain where it is one array), with the strides of `round`.  Sets pop and
 // slot of every block and run descriptor; returns the elements used.
 size_t relayout_slots(wlb_blocks *h, size_t round)
 {
     size_t elems = 0;
     for (size_t r = 0; r < h->runs.size(); ++r) {
         int64_t slot = h->run_slot0[h->unified ? 0 : r];
-        if (round && slot * h->esize >= ((int64_t)64 << 20)) slot = (int64_t)(round_up((size_t)slot * h->esize, round) / h->esize);
+        slot = (int64_t)(slot_stride((size_t)slot * h->esize, round) / h->esize);
         int64_t pop = (int64_t)elems;
         if (h->unified) {  // the run's place in the domain's array
             const DevBlock &R = h->dev[h->nblk + r];
@@ -962,13 +977,13 @@ int autotune(wlb_blocks *h)
     h->overlap = false;
     int rc = set_tiles(h, bs[0], bs[1], bs[2], bg);
     if (rc) return rc;
-    // slot stride: other roundings of the large slots (the state is
-    // initialised again after the autotuner, in whatever layout it keeps)
+    // slot stride: other strides of the large slots (the state is initialised
+    // again after the autotuner, in whatever layout it keeps)
     bool big = false;
-    for (int64_t s0 : h->run_slot0) big = big || s0 * h->esize >= ((int64_t)64 << 20);
+    for (int64_t s0 : h->run_slot0) big = big || s0 * h->esize >= ((int64_t)16 << 20);
     if (big) {
         size_t bround = h->slot_round;
-        for (size_t cand : {(size_t)2 << 20, (size_t)0}) {
+        for (size_t cand : {(size_t)2 << 20, (size_t)0, kSlotSkew}) {
             relayout_slots(h, cand);
             HIPCHK(hipMemcpyAsync(h->arena + h->off_blocks, h->dev.data(), h->dev.size() * sizeof(DevBlock),
                                   hipMemcpyHostToDevice, h->stream));
