@@ -1,5 +1,5 @@
-// misc.hip -- storage-independent kernels: geometry masks, the second pass of
-// the deterministic FP64 conservation reduction, and a bandwidth probe copy.
+// misc.hip -- storage-independent kernels: geometry masks, the later passes of
+// the deterministic FP64 reductions, and a bandwidth probe copy.
 #include "lattice.hpp"
 #include "wlb_internal.hpp"
 
@@ -49,64 +49,70 @@ hipError_t launch_masks(const SweepArgs &a, const uint8_t *solid, int q, int gri
     return hipGetLastError();
 }
 
-// Second pass of the conservation reduction over per-tile partials
-// [n][8] = (sum drho, px, py, pz, kinetic energy, max|u|, n_fluid, -).
-// One workgroup, fixed summation order: the result does not depend on the
-// launch configuration of the first pass.
-__global__ __launch_bounds__(kWG) void reduce_totals_kernel(const double *p, int n, double *out)
-{
-    __shared__ double s[kWG][7];
-    double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int k = threadIdx.x; k < n; k += kWG)
-        for (int j = 0; j < 7; ++j) {
-            const double v = p[(int64_t)k * 8 + j];
-            acc[j] = (j == 5) ? fmax(acc[j], v) : acc[j] + v;
-        }
-    for (int j = 0; j < 7; ++j) s[threadIdx.x][j] = acc[j];
-    __syncthreads();
-    for (int w = kWG / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int j = 0; j < 7; ++j) {
-                const double o = s[threadIdx.x + w][j];
-                s[threadIdx.x][j] = (j == 5) ? fmax(s[threadIdx.x][j], o) : s[threadIdx.x][j] + o;
-            }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[0] = s[0][6] + s[0][0];  // mass = n_fluid + sum (rho - 1)
-        for (int j = 1; j < 7; ++j) out[j] = s[0][j];
-        out[7] = 0.0;
-    }
-}
-
-hipError_t launch_reduce_totals(const double *partials, int n, double *out8, hipStream_t st)
-{
-    hipLaunchKernelGGL(reduce_totals_kernel, dim3(1), dim3(kWG), 0, st, partials, n, out8);
-    return hipGetLastError();
-}
-
-// Second pass of a plain 8-component sum over per-tile partials [n][8], in a
-// fixed order (independent of the first pass's launch configuration).
-__global__ __launch_bounds__(kWG) void reduce_sum8_kernel(const double *p, int n, double *out)
+// Passes after the per-tile partials [n][8]: a sum over each component (the
+// maximum for component 5 of the conservation partials), in a fixed order that
+// does not depend on the first pass's launch.  Workgroup g of a pass takes
+// partials [g per, (g + 1) per).  More than kReduceDirect of them go through
+// kReduceGroups workgroups and a second pass over their sums: one workgroup
+// alone read 128,000 partials (320^3) in 270 us.  MAX: conservation
+// partials (sum drho, px, py, pz, kinetic energy, max|u|, n_fluid, -);
+// FINAL turns sum drho into the mass.
+template <bool MAX, bool FINAL>
+__global__ __launch_bounds__(kWG) void reduce8_kernel(const double *p, int n, int per, double *out)
 {
     __shared__ double s[kWG][8];
+    const int first = blockIdx.x * per, last = n - first < per ? n : first + per;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int k = threadIdx.x; k < n; k += kWG)
-        for (int j = 0; j < 8; ++j) acc[j] += p[(int64_t)k * 8 + j];
+    for (int k = first + threadIdx.x; k < last; k += kWG)
+        for (int j = 0; j < 8; ++j) {
+            const double v = p[(int64_t)k * 8 + j];
+            acc[j] = (MAX && j == 5) ? fmax(acc[j], v) : acc[j] + v;
+        }
     for (int j = 0; j < 8; ++j) s[threadIdx.x][j] = acc[j];
     __syncthreads();
     for (int w = kWG / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w)
-            for (int j = 0; j < 8; ++j) s[threadIdx.x][j] += s[threadIdx.x + w][j];
+            for (int j = 0; j < 8; ++j) {
+                const double o = s[threadIdx.x + w][j];
+                s[threadIdx.x][j] = (MAX && j == 5) ? fmax(s[threadIdx.x][j], o) : s[threadIdx.x][j] + o;
+            }
         __syncthreads();
     }
-    if (threadIdx.x < 8) out[threadIdx.x] = s[0][threadIdx.x];
+    if (threadIdx.x < 8) {
+        const int j = threadIdx.x;
+        double r = s[0][j];
+        if (MAX && FINAL) {
+            if (j == 0) r = s[0][6] + s[0][0];  // mass = n_fluid + sum (rho - 1)
+            if (j == 7) r = 0.0;
+        }
+        out[(int64_t)blockIdx.x * 8 + j] = r;
+    }
 }
 
-hipError_t launch_reduce_sum8(const double *partials, int n, double *out8, hipStream_t st)
+template <bool MAX>
+static hipError_t reduce8(const double *partials, int n, double *groups, double *out8, hipStream_t st)
 {
-    hipLaunchKernelGGL(reduce_sum8_kernel, dim3(1), dim3(kWG), 0, st, partials, n, out8);
+    if (n > kReduceDirect) {
+        const int per = (n + kReduceGroups - 1) / kReduceGroups;
+        const int g = (n + per - 1) / per;
+        hipLaunchKernelGGL((reduce8_kernel<MAX, false>), dim3(g), dim3(kWG), 0, st, partials, n, per, groups);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        partials = groups;
+        n = g;
+    }
+    hipLaunchKernelGGL((reduce8_kernel<MAX, true>), dim3(1), dim3(kWG), 0, st, partials, n, n, out8);
     return hipGetLastError();
+}
+
+hipError_t launch_reduce_totals(const double *partials, int n, double *groups, double *out8, hipStream_t st)
+{
+    return reduce8<true>(partials, n, groups, out8, st);
+}
+
+hipError_t launch_reduce_sum8(const double *partials, int n, double *groups, double *out8, hipStream_t st)
+{
+    return reduce8<false>(partials, n, groups, out8, st);
 }
 
 // Streaming copy, one 16-byte vector per thread over a grid that covers the

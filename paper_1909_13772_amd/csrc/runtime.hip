@@ -89,7 +89,7 @@ struct wlb_blocks {
     int64_t ncells = 0, nfluid = 0, xchg_elems = 0;
     // arena layout (bytes)
     size_t off_pop = 0, pop_bytes = 0, off_mask = 0, mask_words = 0, off_blocks = 0, off_tiles = 0,
-           tile_cap = 0, off_pull = 0, off_push = 0, off_partials = 0, off_totals = 0, off_stage = 0,
+           tile_cap = 0, off_pull = 0, off_push = 0, off_partials = 0, off_totals = 0, off_groups = 0, off_stage = 0,
            stage_bytes = 0, off_mlp = 0, arena_bytes = 0, off_cells = 0, off_ltiles = 0, ltile_cap = 0,
            off_vtiles = 0, vtile_cap = 0, off_strips = 0;
     // sweep tiles of 256 consecutive cells over the domain (unified) or over
@@ -755,8 +755,34 @@ int capture_graph(wlb_blocks *h, int k)
     return WLB_OK;
 }
 
-// Deterministic FP64 totals of the current state into arena totals slot;
-// copies them to `host8` when non-null (synchronises).
+// Density and velocity of every cell; small ones skip the staging area.
+size_t field_bytes(const wlb_blocks *h) { return 4 * sizeof(double) * (size_t)h->ncells; }
+bool small_fields(const wlb_blocks *h) { return field_bytes(h) <= ((size_t)2 << 20); }
+
+// Where the last pass of a reduction writes its eight sums: pinned host
+// memory, which is the caller's after the next synchronisation, or the arena.
+struct Sums {
+    double *at;
+    bool host;
+};
+Sums sums_target(wlb_blocks *h)
+{
+    if (double *p = h->ring.sums()) return Sums{p, true};
+    return Sums{reinterpret_cast<double *>(h->arena + h->off_totals), false};
+}
+// Waits for the stream and hands the sums out.
+int sums_fetch(wlb_blocks *h, const Sums &s, double *out8)
+{
+    if (!s.host) HIPCHK(hipMemcpyAsync(out8, s.at, 8 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    if (s.host) std::memcpy(out8, s.at, 8 * sizeof(double));
+    return WLB_OK;
+}
+
+double *partials_of(wlb_blocks *h) { return reinterpret_cast<double *>(h->arena + h->off_partials); }
+double *groups_of(wlb_blocks *h) { return reinterpret_cast<double *>(h->arena + h->off_groups); }
+
+// Deterministic FP64 totals of the current state (synchronises).
 int compute_totals(wlb_blocks *h, double *host8)
 {
     MomArgs m{};
@@ -765,15 +791,13 @@ int compute_totals(wlb_blocks *h, double *host8)
     m.z0 = 0;
     m.z1 = 0;
     m.out = nullptr;
-    m.partials = reinterpret_cast<double *>(h->arena + h->off_partials);
+    m.partials = partials_of(h);
     HIPCHK(moments_dispatch(h, m, aux_grid(h)));
-    double *tot = reinterpret_cast<double *>(h->arena + h->off_totals);
-    HIPCHK(launch_reduce_totals(m.partials, (int)h->tiles.size(), tot, h->stream));
-    if (host8) {
-        HIPCHK(hipMemcpyAsync(host8, tot, 8 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-        host8[7] = (double)h->steps;
-    }
+    const Sums tot = sums_target(h);
+    HIPCHK(launch_reduce_totals(m.partials, (int)h->tiles.size(), groups_of(h), tot.at, h->stream));
+    const int rc = sums_fetch(h, tot, host8);
+    if (rc) return rc;
+    host8[7] = (double)h->steps;
     return WLB_OK;
 }
 
@@ -1521,6 +1545,8 @@ int wlb_blocks_create(const wlb_block_desc *d, int32_t n, const int32_t domain[3
     off += round_up(cap * 8 * sizeof(double), 256);
     h->off_totals = off;
     off += 256;
+    h->off_groups = off;
+    off += round_up(kReduceGroups * 8 * sizeof(double), 256);
     h->off_mlp = off;
     off += round_up(mlp_dev_bytes(), 256);
     const size_t plane_cells = (size_t)domain[0] * domain[1];
@@ -1555,6 +1581,13 @@ int wlb_blocks_bind(wlb_blocks_t h, void *arena, size_t bytes, void *stream)
     HIPCHK(hipMemcpyAsync(h->arena + h->off_push, h->push.data(), h->push.size() * sizeof(XItem),
                           hipMemcpyHostToDevice, h->stream));
     h->bound = true;
+    // pinned buffers of the field and population transfers (0.2 ms; the first
+    // transfer would pay for them otherwise), failing which copies go direct
+    if (small_fields(h))
+        (void)h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1);
+    else
+        (void)h->ring.reserve(PinnedRing::kChunk);
+    (void)h->ring.sums();
     if (h->overlap) {
         int rc = ensure_stream2(h);
         if (rc) return rc;
@@ -1803,34 +1836,61 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
         int rc = wlb_ghost_exchange(h);
         if (rc) return rc;
     }
-    if (totals) {
-        int rc = compute_totals(h, totals);
+    const int64_t plane = (int64_t)h->dom[0] * h->dom[1];
+    const int64_t N = plane * h->dom[2];
+    const int kz = planes_per_chunk(h, 4 * sizeof(double));
+    if (!rho && !u) return totals ? compute_totals(h, totals) : WLB_OK;
+    // one pass gives fields and totals where the fields fit the staging area
+    const bool whole = kz >= h->dom[2];
+    if (totals && !whole) {
+        const int rc = compute_totals(h, totals);
         if (rc) return rc;
     }
-    if (rho || u) {
-        const int64_t plane = (int64_t)h->dom[0] * h->dom[1];
-        const int64_t N = plane * h->dom[2];
-        const int kz = planes_per_chunk(h, 4 * sizeof(double));
-        double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
+    double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
+    // small fields are written straight into pinned host memory by the kernel
+    // (32^3: 1 MB; four copies of 256 KB cost 14 us each)
+    const bool direct = whole && small_fields(h) && h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1);
+    if (direct) stage = reinterpret_cast<double *>(h->ring.slot(0));
+    const Sums tot = sums_target(h);
+    auto fields = [&](int z0, int z1) -> int {
+        MomArgs m{};
+        m.s = h->args;
+        m.swapped = h->parity;
+        m.z0 = z0;
+        m.z1 = z1;
+        m.out = stage;
+        m.partials = totals && whole ? partials_of(h) : nullptr;
+        HIPCHK(moments_dispatch(h, m, aux_grid(h)));
+        if (m.partials) HIPCHK(launch_reduce_totals(m.partials, (int)h->tiles.size(), groups_of(h), tot.at, h->stream));
+        return WLB_OK;
+    };
+    if (direct) {
+        const int rc = fields(0, h->dom[2]);
+        if (rc) return rc;
+    } else {
         HostCopy down(h->ring, true, h->stream, ((rho ? 1 : 0) + (u ? 3 : 0)) * sizeof(double) * N);
         for (int z0 = 0; z0 < h->dom[2]; z0 += kz) {
             const int z1 = std::min(h->dom[2], z0 + kz);
             const int64_t S = (int64_t)(z1 - z0) * plane;
-            MomArgs m{};
-            m.s = h->args;
-            m.swapped = h->parity;
-            m.z0 = z0;
-            m.z1 = z1;
-            m.out = stage;
-            m.partials = nullptr;
-            HIPCHK(moments_dispatch(h, m, aux_grid(h)));
+            const int rc = fields(z0, z1);
+            if (rc) return rc;
             if (rho) HIPCHK(down.add(rho + z0 * plane, stage, S * sizeof(double)));
             if (u)
                 for (int a = 0; a < 3; ++a)
                     HIPCHK(down.add(u + a * N + z0 * plane, stage + (1 + a) * S, S * sizeof(double)));
         }
         HIPCHK(down.flush());
+    }
+    if (totals && whole) {
+        const int rc = sums_fetch(h, tot, totals);
+        if (rc) return rc;
+        totals[7] = (double)h->steps;
+    } else {
         HIPCHK(hipStreamSynchronize(h->stream));
+    }
+    if (direct) {
+        if (rho) std::memcpy(rho, stage, N * sizeof(double));
+        if (u) std::memcpy(u, stage + N, 3 * N * sizeof(double));
     }
     return WLB_OK;
 }
@@ -1840,13 +1900,10 @@ int wlb_force_get(wlb_blocks_t h, double out[8])
     if (!h || !out) return fail(WLB_ERR_ARG, "null argument");
     if (!h->inited) return fail(WLB_ERR_STATE, "wlb_lbm_init must come first");
     if (h->steps == 0) return fail(WLB_ERR_STATE, "no step since wlb_lbm_init: the force is that of the last step");
-    double *partials = reinterpret_cast<double *>(h->arena + h->off_partials);
-    HIPCHK(force_dispatch(h, partials, aux_grid(h)));
-    double *tot = reinterpret_cast<double *>(h->arena + h->off_totals);
-    HIPCHK(launch_reduce_sum8(partials, (int)h->tiles.size(), tot, h->stream));
-    HIPCHK(hipMemcpyAsync(out, tot, 8 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    return WLB_OK;
+    HIPCHK(force_dispatch(h, partials_of(h), aux_grid(h)));
+    const Sums tot = sums_target(h);
+    HIPCHK(launch_reduce_sum8(partials_of(h), (int)h->tiles.size(), groups_of(h), tot.at, h->stream));
+    return sums_fetch(h, tot, out);
 }
 
 int wlb_debug_write_coverage(wlb_blocks_t h, int32_t odd, uint32_t *counts)

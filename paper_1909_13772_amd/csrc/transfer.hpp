@@ -37,19 +37,18 @@ public:
     {
         for (hipEvent_t e : ev_) (void)hipEventDestroy(e);
         if (base_) (void)hipHostFree(base_);
+        if (small_) (void)hipHostFree(small_);
     }
-    // Room for kSlots pieces of `chunk` bytes; false without pinned memory.
+    // Room for kSlots pieces of `chunk` bytes, one after the other; false
+    // without pinned memory.
     bool reserve(size_t chunk)
     {
+        chunk = (chunk + 4095) & ~(size_t)4095;
         if (chunk > chunk_) {
             if (base_) (void)hipHostFree(base_);
-            base_ = nullptr;
             chunk_ = 0;
-            if (hipHostMalloc(&base_, chunk * kSlots, hipHostMallocDefault) != hipSuccess) {
-                (void)hipGetLastError();
-                base_ = nullptr;
-                return false;
-            }
+            base_ = pinned(chunk * kSlots);
+            if (!base_) return false;
             chunk_ = chunk;
         }
         while ((int)ev_.size() < kSlots) {
@@ -64,41 +63,48 @@ public:
     }
     char *slot(int k) const { return static_cast<char *>(base_) + (size_t)k * chunk_; }
     hipEvent_t event(int k) const { return ev_[k]; }
+    // A few words that kernels write their sums to; null without pinned memory.
+    double *sums()
+    {
+        if (!small_) small_ = pinned(4096);
+        return static_cast<double *>(small_);
+    }
 
 private:
-    void *base_ = nullptr;
+    static void *pinned(size_t n)
+    {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, n, hipHostMallocDefault) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    void *base_ = nullptr, *small_ = nullptr;
     size_t chunk_ = 0;
     std::vector<hipEvent_t> ev_;
 };
 
 // One transfer of about `total` bytes in one direction on one stream, as any
-// number of pieces.  Device-side order is the stream's: a kernel launched
-// before add() has finished when its pieces are read, and one launched after
-// flush() sees every piece written.
+// number of arrays.  An array goes over the link in pieces of up to 4 MB
+// (45-54 GB/s; a piece costs some 9 us beyond its bytes, so small transfers
+// take a quarter of their size), and a piece is copied on the host in parts
+// of 512 KB by whichever thread is free.  Device-side order is the stream's: a
+// kernel launched before add() has finished when its pieces are read, and one
+// launched after flush() sees every piece written.
 class HostCopy {
 public:
     HostCopy(PinnedRing &ring, bool to_host, hipStream_t st, size_t total) : ring_(ring), to_host_(to_host), st_(st)
     {
-        // pieces small enough that copying one overlaps the transfer of the
-        // next also where the whole transfer is small
-        chunk_ = std::min(PinnedRing::kChunk, std::max<size_t>((size_t)256 << 10, total / 16));
+        // a smaller transfer to the device is over (25 GB/s from pageable
+        // memory) before buffers and threads have paid for themselves
+        if (!to_host && total < ((size_t)128 << 20)) return;
+        chunk_ = std::min(PinnedRing::kChunk, std::max<size_t>((size_t)256 << 10, total / 4));
         chunk_ = (chunk_ + 4095) & ~(size_t)4095;
         pinned_ = ring.reserve(chunk_);
         if (!pinned_) return;
         cpu_set_t cs;
         const int cpus = sched_getaffinity(0, sizeof cs, &cs) == 0 ? CPU_COUNT(&cs) : 1;
-        const int want = (int)std::min<size_t>(7, total / ((size_t)3 << 19));  // one more thread per 1.5 MB
-        int dev = 0;
-        (void)hipGetDevice(&dev);
-        try {
-            for (int k = 0; k < std::min(want, cpus - 1); ++k)
-                workers_.emplace_back([this, dev] {
-                    (void)hipSetDevice(dev);
-                    work();
-                });
-        } catch (const std::system_error &) {
-            // fewer threads: the caller's own does the rest
-        }
+        want_ = std::min((int)std::min<size_t>(7, total >> 20), cpus - 1);  // one more thread per MB
+        (void)hipGetDevice(&dev_);
     }
     ~HostCopy()
     {
@@ -111,26 +117,28 @@ public:
     }
     hipError_t add(void *host, void *dev, size_t n)
     {
-        if (!pinned_) {
-            const hipError_t e = to_host_ ? hipMemcpyAsync(host, dev, n, hipMemcpyDeviceToHost, st_)
-                                          : hipMemcpyAsync(dev, host, n, hipMemcpyHostToDevice, st_);
-            return e;
-        }
+        if (!pinned_)
+            return to_host_ ? hipMemcpyAsync(host, dev, n, hipMemcpyDeviceToHost, st_)
+                            : hipMemcpyAsync(dev, host, n, hipMemcpyHostToDevice, st_);
         for (size_t o = 0; o < n; o += chunk_) {
-            Job j{static_cast<char *>(host) + o, static_cast<char *>(dev) + o, std::min(chunk_, n - o), next_};
+            const int k = next_;
             next_ = (next_ + 1) % PinnedRing::kSlots;
-            if (!free_slot(j.slot)) return err_;
+            if (!free_slot(k)) return err_;
+            const size_t m = std::min(chunk_, n - o);
             if (to_host_) {
-                hipError_t e = hipMemcpyAsync(ring_.slot(j.slot), j.dev, j.n, hipMemcpyDeviceToHost, st_);
-                if (e == hipSuccess) e = hipEventRecord(ring_.event(j.slot), st_);
+                hipError_t e = hipMemcpyAsync(ring_.slot(k), static_cast<char *>(dev) + o, m, hipMemcpyDeviceToHost, st_);
+                if (e == hipSuccess) e = hipEventRecord(ring_.event(k), st_);
                 if (e != hipSuccess) return e;
             }
             {
                 std::lock_guard<std::mutex> lk(mu_);
-                busy_[j.slot] = true;
-                queue_.push_back(j);
+                piece_[k] = Piece{static_cast<char *>(dev) + o, m, (int)((m + kPart - 1) / kPart), true};
+                for (size_t q = 0; q < m; q += kPart)
+                    queue_.push_back(Part{static_cast<char *>(host) + o + q, q, std::min(kPart, m - q), k});
             }
-            cv_.notify_one();
+            cv_.notify_all();
+            // threads start while the link is busy with what is under way
+            if ((int)workers_.size() < want_) spawn();
         }
         return hipSuccess;
     }
@@ -145,17 +153,40 @@ public:
     }
 
 private:
-    struct Job {
-        char *host, *dev;
+    static constexpr size_t kPart = (size_t)512 << 10;
+    struct Piece {
+        char *dev;
         size_t n;
+        int left;  // parts not yet copied
+        bool busy;
+    };
+    struct Part {
+        char *host;
+        size_t off, n;
         int slot;
     };
-    // Waits until slot k holds no unfinished piece, working on pieces
+    void spawn()
+    {
+        try {
+            workers_.emplace_back([this] {
+                (void)hipSetDevice(dev_);
+                std::unique_lock<std::mutex> lk(mu_);
+                for (;;) {
+                    cv_.wait(lk, [this] { return done_ || !queue_.empty(); });
+                    if (queue_.empty()) return;
+                    run_one(lk);
+                }
+            });
+        } catch (const std::system_error &) {
+            want_ = 0;  // the threads there are and the caller's own do the rest
+        }
+    }
+    // Waits until slot k holds no unfinished piece, working on parts
     // meanwhile; false after an error.
     bool free_slot(int k)
     {
         std::unique_lock<std::mutex> lk(mu_);
-        while (busy_[k]) {
+        while (piece_[k].busy) {
             if (!queue_.empty())
                 run_one(lk);
             else
@@ -163,45 +194,44 @@ private:
         }
         return err_ == hipSuccess;
     }
-    void work()
-    {
-        std::unique_lock<std::mutex> lk(mu_);
-        for (;;) {
-            cv_.wait(lk, [this] { return done_ || !queue_.empty(); });
-            if (queue_.empty()) return;
-            run_one(lk);
-        }
-    }
-    // Takes the oldest piece and copies it with the lock released.
+    // Takes the oldest part and copies it with the lock released.
     void run_one(std::unique_lock<std::mutex> &lk)
     {
-        const Job j = queue_.front();
+        const Part p = queue_.front();
         queue_.pop_front();
         lk.unlock();
-        const hipError_t e = to_host_ ? to_host(j) : to_device(j);
+        hipError_t e;
+        if (to_host_) {
+            populate(p.host, p.n);
+            e = hipEventSynchronize(ring_.event(p.slot));
+            if (e == hipSuccess) std::memcpy(p.host, ring_.slot(p.slot) + p.off, p.n);
+        } else {
+            // the buffer's previous piece may still be on its way to the device
+            e = hipEventSynchronize(ring_.event(p.slot));
+            if (e == hipSuccess) std::memcpy(ring_.slot(p.slot) + p.off, p.host, p.n);
+        }
         lk.lock();
         if (e != hipSuccess && err_ == hipSuccess) err_ = e;
-        busy_[j.slot] = false;
+        Piece &w = piece_[p.slot];
+        if (--w.left > 0) return;
+        if (!to_host_ && err_ == hipSuccess) {  // the whole piece is in the buffer
+            lk.unlock();
+            e = hipMemcpyAsync(w.dev, ring_.slot(p.slot), w.n, hipMemcpyHostToDevice, st_);
+            if (e == hipSuccess) e = hipEventRecord(ring_.event(p.slot), st_);
+            lk.lock();
+            if (e != hipSuccess && err_ == hipSuccess) err_ = e;
+        }
+        w.busy = false;
         cv_.notify_all();
     }
-    hipError_t to_host(const Job &j)
+    // Maps the pages of a destination in one call: 9 GB/s per thread of 4 KiB
+    // pages against 5 when the copy faults them in one by one.
+    static void populate(char *host, size_t n)
     {
-        const uintptr_t a = reinterpret_cast<uintptr_t>(j.host) & ~(uintptr_t)4095;
-        const uintptr_t b = (reinterpret_cast<uintptr_t>(j.host) + j.n + 4095) & ~(uintptr_t)4095;
+        const uintptr_t a = reinterpret_cast<uintptr_t>(host) & ~(uintptr_t)4095;
+        const uintptr_t b = (reinterpret_cast<uintptr_t>(host) + n + 4095) & ~(uintptr_t)4095;
         constexpr int kPopulateWrite = 23;  // MADV_POPULATE_WRITE; unknown to older kernels, then it does nothing
         (void)madvise(reinterpret_cast<void *>(a), b - a, kPopulateWrite);
-        const hipError_t e = hipEventSynchronize(ring_.event(j.slot));
-        if (e == hipSuccess) std::memcpy(j.host, ring_.slot(j.slot), j.n);
-        return e;
-    }
-    hipError_t to_device(const Job &j)
-    {
-        // the buffer's previous piece may still be on its way to the device
-        hipError_t e = hipEventSynchronize(ring_.event(j.slot));
-        if (e != hipSuccess) return e;
-        std::memcpy(ring_.slot(j.slot), j.host, j.n);
-        e = hipMemcpyAsync(j.dev, ring_.slot(j.slot), j.n, hipMemcpyHostToDevice, st_);
-        return e == hipSuccess ? hipEventRecord(ring_.event(j.slot), st_) : e;
     }
 
     PinnedRing &ring_;
@@ -209,10 +239,11 @@ private:
     hipStream_t st_;
     size_t chunk_ = 0;
     bool pinned_ = false;
+    int want_ = 0, dev_ = 0;
     std::mutex mu_;
     std::condition_variable cv_;
-    std::deque<Job> queue_;
-    bool busy_[PinnedRing::kSlots] = {};
+    std::deque<Part> queue_;
+    Piece piece_[PinnedRing::kSlots] = {};
     bool done_ = false;
     int next_ = 0;
     hipError_t err_ = hipSuccess;

@@ -177,8 +177,10 @@ size_t mlp_dev_bytes();
 
 // Storage-independent kernels (misc.hip).
 hipError_t launch_masks(const SweepArgs &a, const uint8_t *solid, int q, int grid, hipStream_t st);
-hipError_t launch_reduce_totals(const double *partials, int n, double *out8, hipStream_t st);
-hipError_t launch_reduce_sum8(const double *partials, int n, double *out8, hipStream_t st);
+// groups: room for kReduceGroups x 8 intermediate sums.
+constexpr int kReduceDirect = 4096, kReduceGroups = 64;
+hipError_t launch_reduce_totals(const double *partials, int n, double *groups, double *out8, hipStream_t st);
+hipError_t launch_reduce_sum8(const double *partials, int n, double *groups, double *out8, hipStream_t st);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t st);
 hipError_t launch_les_targets(const double *filt, const int32_t nc[3], double tau0, float *raw, float *target,
                               hipStream_t st);
