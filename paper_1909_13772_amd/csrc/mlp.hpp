@@ -17,9 +17,10 @@
 // Each layer computes hidden x cells (transposed) so a lane keeps the column
 // of its own cell: tile A holds cells 0..31 (fed by lanes 0..31 through k
 // 0..7), tile B cells 32..63 (fed by lanes 32..63 through k 8..15), so no
-// data moves between lanes before the last layer.  Layer 2 consumes layer 1's
-// registers directly; the k order this implies is folded into the layout of
-// W2 prepared on the host (MlpDev).
+// data moves between lanes.  Layers 2 and 3 consume the registers of the layer
+// before directly; the k order this implies is folded into the layout of W2
+// and w3 prepared on the host (MlpDev).  w3 fills every row of its operand, so
+// each register of either lane half holds the output of the lane's column.
 #pragma once
 
 #include "lattice.hpp"
@@ -38,11 +39,12 @@ struct alignas(16) MlpDev {
     uint16_t w2[2][64][8];  // layer-2 A operand per k-chunk and lane
     float b1[2][16];        // bias of result register j for lane half h
     float b2[2][16];
-    float w3[2][16];        // bf16-rounded output weights per register
+    uint16_t w3[2][2][8];   // layer-3 A operand per k-chunk and lane half, the same in every row
     float b3;
     float pad[7];
 };
 static_assert(sizeof(MlpDev) % 16 == 0, "MlpDev is copied in 16-byte units");
+static_assert(sizeof(MlpDev) <= WLB_MLP_WORKSPACE, "wlb_mlp_forward keeps it in the caller's workspace");
 
 // Copy the network into a workgroup's shared memory (all threads call it).
 __device__ __forceinline__ void mlp_stage(MlpDev *dst, const void *src)
@@ -136,8 +138,8 @@ __device__ __forceinline__ f32x16_t load_f32x16(const float *p)
 }
 
 // Layers 1-3 for one 32-cell tile: b1op is the layer-1 B operand (the
-// lane's features in its k half, zeros in the other), the result is this
-// lane's half of the output dot product for the tile's cell in its column.
+// lane's features in its k half, zeros in the other), the result is the
+// output (without b3) of the tile's cell in the lane's column.
 // The biases enter as the accumulators' initial values.
 __device__ __forceinline__ float mlp_tile(const MlpDev *__restrict__ P, int lane, int h, const bf16x8_t b1op)
 {
@@ -164,14 +166,22 @@ __device__ __forceinline__ float mlp_tile(const MlpDev *__restrict__ P, int lane
     f32x16_t d = load_f32x16(P->b2[h]);
 #pragma unroll
     for (int q = 0; q < 2; ++q) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_bf16x8(P->w2[q][lane]), g[q], d, 0, 0, 0);
-    const f32x16_t w3 = load_f32x16(P->w3[h]);
-    float part = 0.f;
+    f32x16_t o;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        part = fmaf(w3[j], bf16_round(gelu_erf(d[j])), part);
-        if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    for (int j = 0; j < 16; ++j) o[j] = 0.f;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        float v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            v[t] = gelu_erf(d[8 * q + t]);
+            if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        g[q] = pack_bf16x8(v);
     }
-    return part;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_bf16x8(P->w3[q][h]), g[q], o, 0, 0, 0);
+    return o[0];
 }
 
 // Wave-collective forward pass: every lane of the wavefront must call it
@@ -191,15 +201,12 @@ __device__ __forceinline__ float mlp_forward_wave(const MlpDev *__restrict__ P, 
     bf16x8_t zero;
 #pragma unroll
     for (int t = 0; t < 8; ++t) zero[t] = __builtin_bit_cast(__bf16, (uint16_t)0);
-    float part[2];
+    float o[2];
 #pragma unroll 1
-    for (int tile = 0; tile < 2; ++tile) part[tile] = mlp_tile(P, lane, h, (h == tile) ? xb : zero);
-    const float pA = part[0], pB = part[1];
-    // lane l < 32 owns cell l (tile A), lane l >= 32 owns cell l (tile B);
-    // the other half of each dot product sits in lane l ^ 32.
-    const float send = h ? pA : pB;
-    const float recv = __shfl_xor(send, 32, 64);
-    return (h ? pB : pA) + recv + P->b3;
+    for (int tile = 0; tile < 2; ++tile) o[tile] = mlp_tile(P, lane, h, (h == tile) ? xb : zero);
+    // both lane halves hold the outputs of a tile's 32 cells: lane l < 32
+    // owns cell l of tile A, lane l >= 32 the same of tile B
+    return (h ? o[1] : o[0]) + P->b3;
 }
 
 __device__ __forceinline__ float softplus_f(float o) { return o > 20.f ? o : log1pf(expf(o)); }

@@ -482,20 +482,14 @@ static uint16_t host_bf16_bits(float v)
     if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0x007fffffu) ? 0x40u : 0u));
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
-static float host_bf16_round(float v)
-{
-    uint32_t u = (uint32_t)host_bf16_bits(v) << 16;
-    float r;
-    std::memcpy(&r, &u, 4);
-    return r;
-}
 
 size_t mlp_dev_bytes() { return sizeof(MlpDev); }
 
 // Per-lane operand layout for mlp_forward_wave (see mlp.hpp): layer-1 A
 // operand = W1 row (lane % 32) in both k halves; layer-2 A operand for
 // k-chunk c = W2 row (lane % 32) at the hidden units that the B operand's
-// k slots hold, unit(k = 8 h + t) = 16 c + 8 (t / 4) + 4 h + t % 4.
+// k slots hold, unit(k = 8 h + t) = 16 c + 8 (t / 4) + 4 h + t % 4; layer-3 A
+// operand = w3 at the same units, whatever the row.
 void mlp_prepare(const float *P, void *out)
 {
     MlpDev d;
@@ -511,6 +505,7 @@ void mlp_prepare(const float *P, void *out)
             for (int c = 0; c < 2; ++c) {
                 const int unit = 16 * c + 8 * (t / 4) + 4 * h + (t % 4);
                 d.w2[c][lane][t] = host_bf16_bits(P[kOffW2 + m * kH + unit]);
+                d.w3[c][h][t] = host_bf16_bits(P[kOffW3 + unit]);
             }
         }
     }
@@ -519,7 +514,6 @@ void mlp_prepare(const float *P, void *out)
             const int u = mlp_unit(j, h);
             d.b1[h][j] = P[kOffB1 + u];
             d.b2[h][j] = P[kOffB2 + u];
-            d.w3[h][j] = host_bf16_round(P[kOffW3 + u]);
         }
     d.b3 = P[kOffB3];
     std::memcpy(out, &d, sizeof d);

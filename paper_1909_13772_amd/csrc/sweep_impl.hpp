@@ -1931,7 +1931,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     static_assert(std::is_same<typename Codec<ST>::T, float>::value, "MLP closure runs in FP32");
     const CollParams<T> cp = coll_params<T>(a);
     __shared__ MlpDev net_s;
-    __shared__ T park[Q][kWG];
+    __shared__ T park[Q + 14][kWG];
     mlp_stage(&net_s, a.mlp);
     const MlpDev *net = &net_s;
     for (int t = first_tile(a); t < a.nstiles; t += gridDim.x) {
@@ -1964,23 +1964,45 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         }
         if (!active)
             for (int k = 0; k < 7; ++k) x[k] = 0.f;
-        // Park the populations in shared memory while the network runs and
-        // rebuild the moments from them afterwards: otherwise the compiler
-        // precomputes most of the relaxation before the network and keeps
-        // ~64 values live through it, halving the occupancy.
+        // Park the populations, the moments and Pi in shared memory while the
+        // network runs: otherwise the compiler precomputes most of the
+        // relaxation before the network and keeps ~64 values live through it,
+        // halving the occupancy.  The sweep is bound by vector instructions,
+        // three quarters of them the 64 activations per cell; parking spares
+        // the recomputation of what LDS holds for free (128^3, with layer 3 on
+        // the matrix cores: 112.7 -> 108.3 us per step; a flow with some lanes
+        // in the fallback 121.0 -> 116.3 us).
 #pragma unroll
         for (int i = 0; i < Q; ++i) park[i][threadIdx.x] = f[i];
+        park[Q][threadIdx.x] = m0.drho;
+        park[Q + 1][threadIdx.x] = m0.uu;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            park[Q + 2 + k][threadIdx.x] = m0.u[k];
+            park[Q + 5 + k][threadIdx.x] = m0.j[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 6; ++k) park[Q + 8 + k][threadIdx.x] = P[k];
         asm volatile("" ::: "memory");
         const float o = mlp_forward_wave(net, x);
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int i = 0; i < Q; ++i) f[i] = park[i][threadIdx.x];
-        const Macro<Q, T> m = moments_of<Q, T>(f, cp.F);
+        Macro<Q, T> m;
+        m.drho = park[Q][threadIdx.x];
+        m.rho = T(1) + m.drho;
+        m.uu = park[Q + 1][threadIdx.x];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            m.u[k] = park[Q + 2 + k][threadIdx.x];
+            m.j[k] = park[Q + 5 + k][threadIdx.x];
+        }
         T tau;
         if (bad || !isfinite(o)) {
-            // Smagorinsky fallback (rare lanes): the same Pi and rho as above
+            // Smagorinsky fallback: the same Pi and rho as above
             T Ps[6];
-            pi_pairs<Q, T>(f, m, Ps);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) Ps[k] = park[Q + 8 + k][threadIdx.x];
             tau = tau_smagorinsky<T>(Ps, m.rho, cp.tau0, cp.smag_k);
         } else {
             tau = cp.tau0 + softplus_f(o);
