@@ -1418,10 +1418,19 @@ int wlb_blocks_create(const wlb_block_desc *d, int32_t n, const int32_t domain[3
     // BF16 118, with 250 places per row 171; FP32 190 and 278; a row per box
     // tile 122 and 190, and where that leaves lanes idle 320^3 FP16 675 against
     // 558, 160^3 D3Q27 KBC FP32 258 against 195, 170^3 BF16 104 against 91).
+    // Where the populations stay in the caches shared lines cost less than
+    // the idle lanes (padded / not): FP32 up to 80 MiB (66^3 12.0 / 10.5,
+    // 101 x 53 x 61 11.9 / 10.6, 72 x 120 x 120, 79 MB, 32.3 / 31.5; 102 x 140
+    // x 140, 152 MB, 55.9 / 56.6), the 16-bit types, bound by instructions, as
+    // far as the cache hints reach (150 x 130 x 110 43.0 / 37.8, 130^3 49.8 /
+    // 41.4, 165 x 165 x 160, 166 MB, 75.1 / 70.7), FP64, bound by its accesses,
+    // only up to 48 MiB (50 x 60 x 70 14.6 / 14.0, 34 x 90 x 90 19.8 / 19.7;
+    // 49 x 100 x 100, 74 MB, 30.1 / 30.5).
+    const size_t packed = (size_t)(h->esize == 2 ? 256 : h->esize == 4 ? 80 : 48) << 20;
     bool same_rows = true;
     for (const HostBlock &B : h->rhost) same_rows = same_rows && B.n[0] == domain[0];
     if (same_rows) {
-        h->strip_row = (size_t)domain[0] * h->esize >= 256 ? (int)round_up(domain[0], align_e) : domain[0];
+        h->strip_row = (size_t)domain[0] * h->esize >= 256 && h->pop_bytes > packed ? (int)round_up(domain[0], align_e) : domain[0];
         for (int b = h->unified ? n + (int)runs.size() : n; b < (int)h->dev.size(); ++b)
             strip_region(h->dev[b], b, h->strip_row, h->strips);
     }

@@ -22,8 +22,8 @@ def _solid(dom, seed, share):
     return (rng.random((dom[2], dom[1], dom[0])) < share).astype(np.uint8)
 
 
-# rows of one cell, of a few, just around a strip and its wavefronts, padded to
-# whole lines (160, 250) and not (101 and shorter), and longer than a strip
+# rows of one cell, of a few, just around a strip and its wavefronts, and
+# longer than a strip
 @pytest.mark.parametrize("dom", [(1, 9, 40), (3, 50, 7), (31, 5, 9), (64, 6, 5), (101, 7, 6), (160, 5, 4), (250, 4, 3), (257, 3, 5), (600, 3, 2)])
 @pytest.mark.parametrize("storage", [wlb.F64, wlb.F32, wlb.F16DEV, wlb.BF16DEV])
 def test_strips_match_boxes(dom, storage):
@@ -52,6 +52,30 @@ def test_strips_match_boxes(dom, storage):
             B.close()
     for k, (a, b) in enumerate(zip(*out)):
         assert np.array_equal(a, b), k
+
+
+# arrays of 274, 114 and 206 MB, whose strips pad rows of 250 cells to whole
+# lines, and the same rows just below the sizes from which they do
+@pytest.mark.parametrize("dom,storage", [((250, 170, 170), wlb.BF16DEV), ((250, 120, 50), wlb.F32), ((250, 120, 45), wlb.F64),
+                                         ((250, 160, 160), wlb.BF16DEV), ((250, 75, 50), wlb.F32), ((250, 30, 34), wlb.F64)])
+def test_long_strips_match_boxes(dom, storage):
+    say(f"case long strips {dom} storage {storage}")
+    rho, u = inputs.random_state(dom, seed=9, umag=0.01)
+    p = wlb.make_params(tau=0.7, magic=3 / 16, force=(1e-5, 0.0, 1e-6))
+    out = []
+    for tiles in (None, (64, 4, 1)):
+        B = wlb.Blocks(wlb.single_block(dom), dom, (1, 0, 1), stencil=19, storage=storage)
+        try:
+            if tiles:
+                B.set_tiles(*tiles)
+            B.init(wlb.TRT, p, rho, u, _solid(dom, 5, 0.05) if storage == wlb.F32 else None)
+            for n in (3, 1):
+                B.step(n)
+                out.append(B.moments()[:2])
+        finally:
+            B.close()
+    for k in (0, 1):
+        assert all(np.array_equal(a, b) for a, b in zip(out[k], out[2 + k])), k
 
 
 @pytest.mark.parametrize(
