@@ -15,7 +15,8 @@ library's stream), and the CPU oracle timed on a bounded sample.
 
 Timing: `value` (MLUPS, ms_per_step) is the wall time of the timed steps
 run the way wlb_lbm_step runs them in production, as replays of the
-captured HIP graph of [even sweep, exchange, odd sweep, exchange].  The
+captured HIP graphs of [even sweep, odd sweep] pairs (with an exchange after
+each sweep where the sweeps do not cross the faces themselves).  The
 per-kernel times behind `roofline` come from a second run of the same
 number of steps with per-kernel HIP events on the library's stream (which
 launches the kernels one by one).

@@ -43,7 +43,9 @@
  *     during the call.  Device memory is one arena that the caller allocates
  *     (size from wlb_blocks_create) and binds; the library never allocates
  *     or frees device memory.  The handle owns host-side descriptors, the
- *     captured HIP graph and the tuning state.
+ *     captured HIP graphs, the tuning state, up to 40 MB of pinned host
+ *     memory for transfers and up to seven copying threads (started by the
+ *     first large transfer), all given back by wlb_blocks_destroy.
  *   Streams: all device work is enqueued on the stream given to
  *     wlb_blocks_bind.  Calls that return host data synchronise that stream.
  *     A handle must not be used from two threads at once.
@@ -178,7 +180,10 @@ int wlb_lbm_sweep(wlb_blocks_t h);
  * Exchange the ghost layers that the last sweep requires (after an even sweep
  * the neighbours' outgoing populations are copied into the ghost layer;
  * after an odd sweep the populations written into the ghost layer are
- * copied into the neighbours).  Idempotent; asynchronous. */
+ * copied into the neighbours).  Where the blocks lie in one array over the
+ * domain and the sweep crosses block and periodic faces itself there is
+ * nothing to move and nothing is launched; a later odd sweep of another kind
+ * that reads ghost cells gets them first.  Idempotent; asynchronous. */
 int wlb_ghost_exchange(wlb_blocks_t h);
 
 /* Moments (Eq. 1) of the current state: rho[N] and u[3][N] (host, may be
@@ -260,7 +265,9 @@ int wlb_info(wlb_blocks_t h, wlb_info_t *out);
  * 8 XCDs round-robin); -1 = one workgroup per tile, the workgroups of each
  * XCD taking one contiguous range of tiles (and of exchange items), so that
  * neighbouring tiles share an L2; > 0 = a persistent grid of that many
- * workgroups looping over the tiles.  tx = 0 packs whole x rows; tx = -1
+ * workgroups looping over the tiles.  tx = 0 packs whole x rows (the sweeps
+ * then run over strips of 256 consecutive cells unless the LDS-staged odd
+ * sweep, the overlap or per-class shapes need boxes); tx = -1
  * makes the sweeps run over lists of up to 256 fluid cells of one block
  * (no lanes on solid cells; needs a preceding wlb_lbm_init with solid cells
  * and blocks of at most 1024 x 1024 x 4096 cells), all other passes over

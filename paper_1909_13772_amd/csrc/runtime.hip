@@ -3,7 +3,8 @@
 // Blocks (paper Sec. 3.1, Sec. 4.1) become descriptors of one device arena
 // that the caller allocates; a time step is a sweep over all blocks followed
 // by a ghost-layer exchange (Sec. 4.2), the exchange between blocks of the
-// same device being a direct copy without buffers (Sec. 3.3).  Host arrays
+// same device being a direct copy without buffers (Sec. 3.3) and none at all
+// where the blocks lie in one array over the domain.  Host arrays
 // are copied in at set-up and out after many steps (Sec. 4.3).
 #include <algorithm>
 #include <array>

@@ -9,12 +9,14 @@
 // closure; bounce-back and pressure (anti-bounce-back) boundaries; Guo body
 // force.  Populations are stored as deviations d_i = f_i - w_i.
 //
-// Streaming uses the in-place AA pattern on one array per block:
+// Streaming uses the in-place AA pattern on one array over the domain (on
+// one array per x-run where the domain's would span 2 GiB and more per slot):
 //   even sweep: read slot i of x, collide, write f*_i into slot opp(i) of x
 //               (no neighbour access);
-//   odd sweep : read the incoming f_i from slot opp(i) of x - c_i (the ghost
-//               layer when outside the block), collide, write f*_i into slot
-//               i of x + c_i.
+//   odd sweep : read the incoming f_i from slot opp(i) of x - c_i (wrapped at
+//               the domain's periodic faces, or from the ghost layer when
+//               outside the run's array), collide, write f*_i into slot i of
+//               x + c_i.
 // Each cell of the odd sweep reads and writes exactly the set
 // {(x + c_j, j)}, so the update is race-free in place.  Bounce-back links
 // (solid neighbour or wall) use the cell's own slots; anti-bounce-back links
