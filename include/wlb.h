@@ -43,9 +43,9 @@
  *     during the call.  Device memory is one arena that the caller allocates
  *     (size from wlb_blocks_create) and binds; the library never allocates
  *     or frees device memory.  The handle owns host-side descriptors, the
- *     captured HIP graphs, the tuning state, up to 40 MB of pinned host
- *     memory for transfers and up to seven copying threads (started by the
- *     first large transfer), all given back by wlb_blocks_destroy.
+ *     captured HIP graphs, the tuning state and up to 40 MB of pinned host
+ *     memory for transfers, all given back by wlb_blocks_destroy.  A large
+ *     transfer runs up to seven copying threads of its own until it returns.
  *   Streams: all device work is enqueued on the stream given to
  *     wlb_blocks_bind.  Calls that return host data synchronise that stream.
  *     A handle must not be used from two threads at once.
