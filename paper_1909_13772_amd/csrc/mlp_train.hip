@@ -3,13 +3,14 @@
 //
 // Loss over a minibatch of n samples: L = (1/n) sum_s ((softplus(o_s) - t_s)
 // * inv_scale)^2, o = network output for the sample's raw features (see
-// mlp.hpp for the network).  The GEMM operands (weights, x, h1, h2) are rounded
-// to bf16 exactly where the sweep's forward rounds them; the rounding has the
-// straight-through gradient, and the gradients themselves keep FP32 precision.
-// Parameter gradients are summed per workgroup in a fixed order, then over
-// workgroups in a fixed order (deterministic).  Adam keeps FP32 master weights; mean / inv_std are not
-// trained.
-#include <algorithm>
+// mlp.hpp for the network).  The forward/backward pass runs in FP32 with the
+// GEMM operands (weights, x, h1, h2) rounded to bf16 exactly where the
+// matrix-core forward rounds them, from FP32 values like there; the rounding
+// has the straight-through gradient.  Every sum has one fixed order of FP32
+// additions: over a layer's inputs in turn, over 64 samples in turn, over the
+// four such sums of 256 samples, then over those (deterministic, and the same
+// whatever the launch).  Adam keeps FP32 master weights; mean / inv_std are
+// not trained.
 #include <cstring>
 #include <mutex>
 
@@ -22,6 +23,10 @@ constexpr int kIn = 7, kH = 32;
 constexpr int kOffMean = 0, kOffIstd = 7, kOffW1 = 14, kOffB1 = kOffW1 + kH * kIn, kOffW2 = kOffB1 + kH,
               kOffB2 = kOffW2 + kH * kH, kOffW3 = kOffB2 + kH, kOffB3 = kOffW3 + kH, kNParam = kOffB3 + 1;
 static_assert(kNParam == 1359, "parameter count");
+constexpr int kChunk = 64;       // samples of one chain of sums
+constexpr int kGradWG = 1024;    // threads per kWG samples
+static_assert(kWG == 4 * kChunk && kGradWG == 4 * kWG, "four chunks, four wavefronts for each");
+
 // GELU and its slope at z, from one evaluation of the CDF's parts.
 __device__ __forceinline__ void gelu_and_slope(float z, float &g, float &slope)
 {
@@ -32,329 +37,274 @@ __device__ __forceinline__ void gelu_and_slope(float z, float &g, float &slope)
 }
 __device__ __forceinline__ float sigmoid_f(float o) { return 1.0f / (1.0f + expf(-o)); }
 
-// x as the sum of three bf16 values (8 + 8 + 8 significand bits: nothing of
-// an FP32 value is lost; the differences are exact).  A value that bf16
-// rounds to infinity keeps it in the first part alone.
-struct Split3 {
-    __bf16 p[3];
+// One quantity of kWG samples for the kH units of a layer: rows of kH floats,
+// whose quads are permuted by the sample so that one quad of 64 samples
+// spreads over all banks.
+struct alignas(16) UnitRows {
+    float v[kWG][kH];
+    __device__ __forceinline__ float4 &quad(int s, int k4) { return *reinterpret_cast<float4 *>(&v[s][((k4 ^ s) & 7) * 4]); }
+    __device__ __forceinline__ float &at(int s, int k) { return v[s][(((k >> 2) ^ s) & 7) * 4 + (k & 3)]; }
 };
-__device__ __forceinline__ Split3 split3(float x)
-{
-    Split3 r;
-    r.p[0] = (__bf16)x;
-    float d = x - (float)r.p[0];
-    d = fabsf(x) < 3e38f ? d : 0.f;
-    r.p[1] = (__bf16)d;
-    r.p[2] = (__bf16)(d - (float)r.p[1]);
-    return r;
-}
+// Shared memory of the gradient kernel.
+struct alignas(16) GradLds {
+    float w1[kH][8];             // bf16-rounded weights; the last column is not used
+    float w2[kH][kH], w2t[kH][kH];
+    float w3[kH], b1[kH], b2[kH];
+    alignas(16) float go[kWG];   // d loss / d o
+    alignas(16) float sq[kWG];   // squared residual
+    alignas(16) float x[kWG][8]; // bf16-rounded features, then 1 (the inputs of W1 and b1)
+    float b3;
+    UnitRows h1, h2, gz1, gz2;   // activations and d loss / d z of both layers
+};
+static_assert(sizeof(GradLds) <= 160 * 1024 && sizeof(UnitRows) >= sizeof(float) * 4 * (kNParam + 1), "shared memory");
 
-// Whether an FP32 activation lies within 8 units in the last place of a bf16
-// rounding boundary: its FP32 error (some 3e-7 relative) may then put it on
-// the other side, which changes the bf16 operand by 2^-8.
-__device__ __forceinline__ bool near_boundary(float g)
-{
-    return ((__float_as_uint(g) & 0xffffu) - (0x8000u - 8u)) <= 16u;
-}
-// GELU in FP64 to 1.5e-9, rounded to bf16 through FP32.  erfc(u) = t
-// exp(-u^2 + P(2 t - 1)), t = 1 / (1 + u / 2), the form that half_erfc_parts
-// uses, with P the degree-13 Chebyshev interpolant of log(erfc(u) exp(u^2) / t)
-// on 0 < t <= 1 (largest deviation 1.2e-9); exp by 2^k times the Taylor sum of
-// the remainder to degree 8 (2e-10).
-__device__ __noinline__ __bf16 gelu_bf16(double z)
-{
-    const double u = fabs(z) * 0.70710678118654752440;
-    const double t = 1.0 / fma(0.5, u, 1.0), s = fma(2.0, t, -1.0);
-    constexpr double c[14] = {-0.6717940851517218,     0.6726432205460087,      0.04734341752106161,
-                              -0.046895482161005086,   -0.0098745349182224,     0.008823558177735913,
-                              0.001770666118369054,    -0.002339277724317185,   -0.00018278214127144218,
-                              0.0006579538480657341,   -3.211377267356806e-05,  -0.0001546337909289383,
-                              1.3371503605768667e-05,  2.0723070945002116e-05};
-    double p = c[13];
-#pragma unroll
-    for (int k = 12; k >= 0; --k) p = fma(p, s, c[k]);
-    const double x = fmax(fma(-u, u, p), -700.0);
-    const double k = rint(x * 1.4426950408889634);
-    const double r = fma(-k, 0.6931471805599453, x);
-    double e = 1.0 / 40320.0;
-    e = fma(e, r, 1.0 / 5040.0);
-    e = fma(e, r, 1.0 / 720.0);
-    e = fma(e, r, 1.0 / 120.0);
-    e = fma(e, r, 1.0 / 24.0);
-    e = fma(e, r, 1.0 / 6.0);
-    e = fma(e, r, 0.5);
-    e = fma(e, r, 1.0);
-    e = fma(e, r, 1.0);
-    const double tail = z * (0.5 * t * ldexp(e, (int)k));  // z Phi(-|z|)
-    return (__bf16)(float)(z >= 0.0 ? z - tail : tail);
-}
-
-constexpr int kGradWG = 512;        // eight wavefronts, each one tile of 32 samples at a time
-constexpr int kGradWaves = kGradWG / 64;
-constexpr int kTileS = 32;          // samples of a wavefront's tile
-constexpr int kMaxGradWG = 512;     // partial rows; larger minibatches loop
-constexpr int kRow = kTileS + 8;    // bf16 per LDS row: 16-byte aligned 8-sample reads, rows spread over the banks
-// LDS rows of a wavefront's tile, each one quantity of its 32 samples
-constexpr int kRowG = 0, kRowH1 = 96, kRowH2 = 128, kRowX = 160, kRowGo = 168, kRows = 171;
-
-typedef __bf16 bf16row_t[kRow];
-
-// Eight consecutive samples of a row as a matrix operand.
-__device__ __forceinline__ bf16x8_t row8(const bf16row_t &r, int s) { return *reinterpret_cast<const bf16x8_t *>(&r[s]); }
-
-// Forward and backward pass of the network over a minibatch on the matrix
-// cores; per-workgroup gradient partials [gridDim.x][kNParam + 1] (last
-// entry: sum of squared residuals).
+// Forward and backward pass of the network; one row of gradient partials per
+// kWG samples, [gridDim.x][kNParam + 1] (last entry: sum of squared
+// residuals).
 //
-// A wavefront takes 32 samples.  Forward (mlp.hpp's layout): lane l holds the
-// sample l % 32 and, in its result registers j, the hidden units mlp_unit(j,
-// l / 32); one layer's registers are the next product's operand.  The same
-// holds for the backward product with W2^T, whose other operand is FP32: it
-// enters as three bf16 parts (split3), three products instead of one, so
-// nothing of its 24 bits is lost.  The weight gradients contract over the
-// samples: both operands are turned through LDS (rows of one quantity, 32
-// samples) and summed over all of a wavefront's tiles in the accumulators of
-// dW2 = gz2^T h1, dW1 and db1 = gz1^T [x | 1], db2 = gz2^T [x | 1], dw3 = h2^T go.
+// A layer's 256 x 32 outputs are shared out as two samples x four units per
+// lane, all units of a wavefront the same: one broadcast read of four weights
+// serves eight additions.  Forward products of two bf16 values are exact in
+// FP32, so the fused multiply-add rounds like a product and a sum.  The
+// parameter sums take one wavefront for rows 0..15 and one for rows 16..31 of
+// W2 (4 x 2 sums per lane), one for W1 and b1 and one for the rest, per chunk;
+// the wavefronts of a chunk run on one SIMD, so that the four SIMDs carry the
+// same load.
 //
-// The bf16 operands h1 and h2 are decided in FP64 where the FP32 activation
-// lies next to a rounding boundary (about one in 3,900): the few that FP32
-// decides the other way were most of the gradient's error against FP64 (6e-7
-// to 1.6e-6 of its norm for 16,384 samples, as with one sample per thread).
-//
-// What bounds it: the activations (GELU and its slope, 64 per sample) on the
-// vector ALUs, some 1,700 instructions per tile against 23 matrix products of
-// 32 cycles.  16,384 samples: 64 workgroups of eight wavefronts, one tile each.
-// One sample per thread on the vector ALUs with the sums read back from LDS
-// took 86 us for that minibatch.
+// What bounds it: the vector ALUs of the CUs that have a workgroup (some 9,000
+// instructions per 64 samples, two thirds of them the products and sums that
+// are made one after the other).  With the reduction, us per call one after
+// another: 16,384 samples 20.7, 262,144 samples 92; one thread per sample with
+// all sums read back from LDS took 100 and 560 for the same bits.
 __global__ __launch_bounds__(kGradWG) void mlp_grad_kernel(const float *__restrict__ P, const float *__restrict__ raw,
                                                            const float *__restrict__ target, int64_t n,
                                                            float inv_scale, float *__restrict__ partial)
 {
-    constexpr size_t kTileBytes = sizeof(__bf16) * kGradWaves * kRows * kRow;
-    constexpr size_t kRedBytes = sizeof(float) * kGradWaves * (kNParam + 1);
-    __shared__ __align__(16) unsigned char smem[kTileBytes > kRedBytes ? kTileBytes : kRedBytes];
-    __shared__ float sw[kNParam];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int m = lane & 31, h = lane >> 5;
-    for (int k = threadIdx.x; k < kNParam; k += kGradWG) sw[k] = P[k];
-    __syncthreads();
-    // operands: W1 row m (both k halves), W2 row m and W2 column m in the
-    // order in which the result registers hold the hidden units
-    bf16x8_t w1, w2[2], w2t[2];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        w1[t] = t < kIn ? (__bf16)sw[kOffW1 + m * kIn + t] : (__bf16)0.f;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int unit = mlp_unit(8 * q + t, h);
-            w2[q][t] = (__bf16)sw[kOffW2 + m * kH + unit];
-            w2t[q][t] = (__bf16)sw[kOffW2 + unit * kH + m];
+    __shared__ __align__(16) GradLds L;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t s0 = (int64_t)blockIdx.x * kWG;
+    {
+        const float w = bf16_round(P[kOffW2 + tid]);
+        L.w2[tid / kH][tid % kH] = w;
+        L.w2t[tid % kH][tid / kH] = w;
+        if (tid < kH * kIn) L.w1[tid / kIn][tid % kIn] = bf16_round(P[kOffW1 + tid]);
+        if (tid < kH) {
+            L.w3[tid] = bf16_round(P[kOffW3 + tid]);
+            L.b1[tid] = P[kOffB1 + tid];
+            L.b2[tid] = P[kOffB2 + tid];
+        }
+        if (tid == 0) L.b3 = P[kOffB3];
+        for (int e = tid; e < kWG * 8; e += kGradWG) {
+            const int k = e & 7;
+            const int64_t s = s0 + (e >> 3);
+            float x = 1.f;
+            if (k < kIn) x = bf16_round(((s < n ? raw[s * kIn + k] : 0.f) - P[kOffMean + k]) * P[kOffIstd + k]);
+            L.x[e >> 3][k] = x;
         }
     }
-    bf16row_t *T = reinterpret_cast<bf16row_t *>(smem) + wv * kRows;
-    f32x16_t dw2 = {}, dw1 = {}, db2 = {}, dw3 = {};
-    float loss = 0.f, db3 = 0.f;
-    const bf16x8_t zero = {};
-    const int64_t ntile = (n + kTileS - 1) / kTileS;
-    // every wavefront of the workgroup makes the same number of rounds
-    for (int64_t t0 = (int64_t)blockIdx.x * kGradWaves; t0 < ntile; t0 += (int64_t)gridDim.x * kGradWaves) {
-        const int64_t s = (t0 + wv) * kTileS + m;
-        const bool act = s < n;
-        // an opaque zero keeps the reads of biases and output weights inside
-        // the loop: hoisted, they would hold ~60 registers
-        int zo = 0;
-        asm volatile("" : "+v"(zo));
-        const float *sv = sw + 4 * h + zo;  // unit mlp_unit(j, h) is 8 (j / 4) + j % 4 further on
-        // ---- forward
-        bf16x8_t xb;
+    __syncthreads();
+    // ---- forward
+    const int u4 = wv & 7, u0 = 4 * u4;         // the lane's units
+    const int sa = 128 * (wv >> 3) + lane;      // and samples sa, sa + 64
+    float s1[2][4], s2[2][4];                   // slopes
+    {
+        float z[2][4] = {};
 #pragma unroll
-        for (int k = 0; k < kIn; ++k) {
-            const float r = act ? raw[s * kIn + k] : 0.f;
-            xb[k] = (__bf16)((r - sw[kOffMean + k + zo]) * sw[kOffIstd + k + zo]);
-        }
-        xb[7] = (__bf16)0.f;
-        if (h == 0) {
+        for (int r = 0; r < 2; ++r) {
+            const float4 xa = *reinterpret_cast<const float4 *>(&L.x[sa + 64 * r][0]);
+            const float4 xb = *reinterpret_cast<const float4 *>(&L.x[sa + 64 * r][4]);
 #pragma unroll
-            for (int k = 0; k < kIn; ++k) T[kRowX + k][m] = xb[k];
-            T[kRowX + kIn][m] = (__bf16)1.f;
-        }
-        f32x16_t z;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) z[j] = sv[kOffB1 + mlp_unit(j, 0)];
-        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, h == 0 ? xb : zero, z, 0, 0, 0);
-        float s1[16];  // slopes of layer 1
-        bf16x8_t hb[2];
-        uint32_t near = 0;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            float g;
-            gelu_and_slope(z[j], g, s1[j]);
-            hb[j / 8][j % 8] = (__bf16)g;
-            T[kRowH1 + mlp_unit(j, h)][m] = (__bf16)g;
-            near |= act && near_boundary(g) ? 1u << j : 0u;
-            // a few activations at a time: all sixteen in flight spill
-            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-        __syncthreads();
-        if (__any(near != 0)) {
-#pragma unroll 1
-            while (near) {
-                const int u = mlp_unit(__builtin_ctz(near), h);
-                double zd = sw[kOffB1 + u];
-#pragma unroll 1
-                for (int k = 0; k < kIn; ++k)
-                    zd = fma((double)bf16_round(sw[kOffW1 + u * kIn + k]), (double)(float)T[kRowX + k][m], zd);
-                T[kRowH1 + u][m] = gelu_bf16(zd);
-                near &= near - 1;
+            for (int j = 0; j < 4; ++j) {
+                const float *w = L.w1[u0 + j];
+                float a = fmaf(w[0], xa.x, 0.f);
+                a = fmaf(w[1], xa.y, a);
+                a = fmaf(w[2], xa.z, a);
+                a = fmaf(w[3], xa.w, a);
+                a = fmaf(w[4], xb.x, a);
+                a = fmaf(w[5], xb.y, a);
+                a = fmaf(w[6], xb.z, a);
+                z[r][j] = a + L.b1[u0 + j];
             }
-#pragma unroll
-            for (int j = 0; j < 16; ++j) hb[j / 8][j % 8] = T[kRowH1 + mlp_unit(j, h)][m];
         }
-        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 16; ++j) z[j] = sv[kOffB2 + mlp_unit(j, 0)];
+        for (int r = 0; r < 2; ++r) {
+            float g[4];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2[q], hb[q], z, 0, 0, 0);
-        float gz[16];  // w3 times the slope of layer 2
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            float g, sl;
-            gelu_and_slope(z[j], g, sl);
-            hb[j / 8][j % 8] = (__bf16)g;
-            T[kRowH2 + mlp_unit(j, h)][m] = (__bf16)g;
-            near |= act && near_boundary(g) ? 1u << j : 0u;
-            gz[j] = bf16_round(sv[kOffW3 + mlp_unit(j, 0)]) * sl;
-            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            for (int j = 0; j < 4; ++j) gelu_and_slope(z[r][j], g[j], s1[r][j]);
+            L.h1.quad(sa + 64 * r, u4) = make_float4(bf16_round(g[0]), bf16_round(g[1]), bf16_round(g[2]), bf16_round(g[3]));
         }
-        if (__any(near != 0)) {
-#pragma unroll 1
-            while (near) {
-                const int u = mlp_unit(__builtin_ctz(near), h);
-                double zd = sw[kOffB2 + u];
+    }
+    __syncthreads();
+    {
+        float z[2][4] = {};
 #pragma unroll 2
-                for (int k = 0; k < kH; ++k)
-                    zd = fma((double)bf16_round(sw[kOffW2 + u * kH + k]), (double)(float)T[kRowH1 + k][m], zd);
-                T[kRowH2 + u][m] = gelu_bf16(zd);
-                near &= near - 1;
-            }
+        for (int k4 = 0; k4 < kH / 4; ++k4) {
+            const float4 h[2] = {L.h1.quad(sa, k4), L.h1.quad(sa + 64, k4)};
 #pragma unroll
-            for (int j = 0; j < 16; ++j) hb[j / 8][j % 8] = T[kRowH2 + mlp_unit(j, h)][m];
+            for (int j = 0; j < 4; ++j) {
+                const float4 w = *reinterpret_cast<const float4 *>(&L.w2[u0 + j][4 * k4]);
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+                    z[r][j] = fmaf(w.w, h[r].w, fmaf(w.z, h[r].z, fmaf(w.y, h[r].y, fmaf(w.x, h[r].x, z[r][j]))));
+            }
         }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            float g[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) gelu_and_slope(z[r][j] + L.b2[u0 + j], g[j], s2[r][j]);
+            L.h2.quad(sa + 64 * r, u4) = make_float4(bf16_round(g[0]), bf16_round(g[1]), bf16_round(g[2]), bf16_round(g[3]));
+        }
+    }
+    __syncthreads();
+    if (tid < kWG) {
+        const bool act = s0 + tid < n;
         float o = 0.f;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) o = fmaf(bf16_round(sv[kOffW3 + mlp_unit(j, 0)]), (float)hb[j / 8][j % 8], o);
-        o += __shfl_xor(o, 32, 64);  // the other half of the units
-        o += sw[kOffB3];
-        // ---- backward
-        const float res = act ? (softplus_f(o) - target[s]) * inv_scale : 0.f;
-        const float go = act ? 2.f * res * inv_scale * sigmoid_f(o) / (float)n : 0.f;
-        if (h == 0) {
-            loss += res * res;
-            db3 += go;
-            const Split3 g3 = split3(go);
-#pragma unroll
-            for (int p = 0; p < 3; ++p) T[kRowGo + p][m] = g3.p[p];
+        for (int k4 = 0; k4 < kH / 4; ++k4) {
+            const float4 h = L.h2.quad(tid, k4);
+            const float4 w = *reinterpret_cast<const float4 *>(&L.w3[4 * k4]);
+            o = fmaf(w.w, h.w, fmaf(w.z, h.z, fmaf(w.y, h.y, fmaf(w.x, h.x, o))));
         }
-        bf16x8_t gb[3][2];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const Split3 g3 = split3(go * gz[j]);
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                gb[p][j / 8][j % 8] = g3.p[p];
-                T[kRowG + 32 * p + mlp_unit(j, h)][m] = g3.p[p];
-            }
-        }
-        f32x16_t ga = {};
-#pragma unroll
-        for (int p = 2; p >= 0; --p)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) ga = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w2t[q], gb[p][q], ga, 0, 0, 0);
-        __syncthreads();
-        // ---- sums over the tile's samples, 16 at a time
-        bf16x8_t xc[2];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int s8 = 16 * c + 8 * h;
-            const bf16x8_t h1 = row8(T[kRowH1 + m], s8);
-            xc[c] = m < 8 ? row8(T[kRowX + (m & 7)], s8) : zero;
-            const bf16x8_t gc = m < 3 ? row8(T[kRowGo + (m < 3 ? m : 0)], s8) : zero;
-            dw3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row8(T[kRowH2 + m], s8), gc, dw3, 0, 0, 0);
-#pragma unroll
-            for (int p = 2; p >= 0; --p) {
-                const bf16x8_t g = row8(T[kRowG + 32 * p + m], s8);
-                dw2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, h1, dw2, 0, 0, 0);
-                db2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(g, xc[c], db2, 0, 0, 0);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const Split3 g3 = split3(ga[j] * s1[j]);
-#pragma unroll
-            for (int p = 0; p < 3; ++p) T[kRowG + 32 * p + mlp_unit(j, h)][m] = g3.p[p];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int p = 2; p >= 0; --p)
-                dw1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row8(T[kRowG + 32 * p + m], 16 * c + 8 * h), xc[c], dw1, 0, 0,
-                                                              0);
-        __syncthreads();
-    }
-    // ---- the eight wavefronts' sums, in a fixed order
-    float *red = reinterpret_cast<float *>(smem) + wv * (kNParam + 1);
-    for (int k = lane; k < kOffW1; k += 64) red[k] = 0.f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {  // lane: column m of each product, rows = units
-        const int u = mlp_unit(j, h);
-        red[kOffW2 + u * kH + m] = dw2[j];
-        if (m < kIn) red[kOffW1 + u * kIn + m] = dw1[j];
-        if (m == kIn) {
-            red[kOffB1 + u] = dw1[j];
-            red[kOffB2 + u] = db2[j];
-        }
-        // the three parts of go sit in columns 0, 1, 2
-        const float a = __shfl_down(dw3[j], 1, 64), b = __shfl_down(dw3[j], 2, 64);
-        if (m == 0) red[kOffW3 + u] = (b + a) + dw3[j];
-    }
-    for (int d = 16; d > 0; d >>= 1) {
-        loss += __shfl_xor(loss, d, 64);
-        db3 += __shfl_xor(db3, d, 64);
-    }
-    if (lane == 0) {
-        red[kOffB3] = db3;
-        red[kNParam] = loss;
+        o += L.b3;
+        const float res = act ? (softplus_f(o) - target[s0 + tid]) * inv_scale : 0.f;
+        L.go[tid] = act ? 2.f * res * inv_scale * sigmoid_f(o) / (float)n : 0.f;
+        L.sq[tid] = res * res;
     }
     __syncthreads();
-    const float *all = reinterpret_cast<const float *>(smem);
-    for (int p = threadIdx.x; p <= kNParam; p += kGradWG) {
-        float a = 0.f;
-        for (int w = 0; w < kGradWaves; ++w) a += all[w * (kNParam + 1) + p];
-        partial[(int64_t)blockIdx.x * (kNParam + 1) + p] = a;
+    // ---- backward
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const float go = L.go[sa + 64 * r];
+        float g[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) g[j] = go * L.w3[u0 + j] * s2[r][j];
+        L.gz2.quad(sa + 64 * r, u4) = make_float4(g[0], g[1], g[2], g[3]);
+    }
+    __syncthreads();
+    {
+        float a[2][4] = {};
+#pragma unroll 2
+        for (int j4 = 0; j4 < kH / 4; ++j4) {
+            const float4 g[2] = {L.gz2.quad(sa, j4), L.gz2.quad(sa + 64, j4)};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 w = *reinterpret_cast<const float4 *>(&L.w2t[u0 + k][4 * j4]);
+#pragma unroll
+                for (int r = 0; r < 2; ++r) a[r][k] = (((a[r][k] + g[r].x * w.x) + g[r].y * w.y) + g[r].z * w.z) + g[r].w * w.w;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+            L.gz1.quad(sa + 64 * r, u4) =
+                make_float4(a[r][0] * s1[r][0], a[r][1] * s1[r][1], a[r][2] * s1[r][2], a[r][3] * s1[r][3]);
+    }
+    __syncthreads();
+    // ---- parameter sums over the chunk's samples, one after the other
+    const int role = wv >> 2, chunk = wv & 3, q0 = chunk * kChunk;
+    float a[4][2] = {};
+    float loss = 0.f;
+    const int r4 = role < 2 ? 4 * role + (lane >> 4) : lane >> 3;          // rows 4 r4 ... of W2, W1
+    const int c0 = role < 2 ? 2 * (lane & 15) : role == 2 ? lane & 7 : lane & 31;  // first column
+    // q0 is a multiple of 8: eight samples at a time, the places of a row's
+    // quads are the same eight for every group
+    if (role < 2) {
+#pragma unroll 8
+        for (int q = q0; q < q0 + kChunk; ++q) {
+            const float4 g = L.gz2.quad(q, r4);
+            const float2 h = *reinterpret_cast<const float2 *>(&L.h1.at(q, c0));
+            a[0][0] += g.x * h.x;
+            a[0][1] += g.x * h.y;
+            a[1][0] += g.y * h.x;
+            a[1][1] += g.y * h.y;
+            a[2][0] += g.z * h.x;
+            a[2][1] += g.z * h.y;
+            a[3][0] += g.w * h.x;
+            a[3][1] += g.w * h.y;
+        }
+    } else if (role == 2) {
+#pragma unroll 8
+        for (int q = q0; q < q0 + kChunk; ++q) {
+            const float4 g = L.gz1.quad(q, r4);
+            const float x = L.x[q][c0];
+            a[0][0] += g.x * x;
+            a[1][0] += g.y * x;
+            a[2][0] += g.z * x;
+            a[3][0] += g.w * x;
+        }
+    } else {
+        // lanes 0..31: b2; lanes 32..63: w3; every lane: b3
+        UnitRows &V = lane < kH ? L.gz2 : L.h2;
+#pragma unroll 8
+        for (int q = q0; q < q0 + kChunk; ++q) {
+            const float go = L.go[q];
+            a[0][0] += V.at(q, c0) * (lane < kH ? 1.f : go);
+            a[1][0] += go;
+        }
+        if (chunk == 0)
+#pragma unroll 8
+            for (int q = 0; q < kWG; q += 4) {
+                const float4 v = *reinterpret_cast<const float4 *>(&L.sq[q]);
+                loss = (((loss + v.x) + v.y) + v.z) + v.w;
+            }
+    }
+    __syncthreads();
+    // ---- the four chunks' sums in turn
+    float(*red)[kNParam + 1] = reinterpret_cast<float(*)[kNParam + 1]>(&L.gz1);
+    float *out = red[chunk];
+    if (role < 2) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            out[kOffW2 + (4 * r4 + j) * kH + c0] = a[j][0];
+            out[kOffW2 + (4 * r4 + j) * kH + c0 + 1] = a[j][1];
+        }
+    } else if (role == 2) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[c0 < kIn ? kOffW1 + (4 * r4 + j) * kIn + c0 : kOffB1 + 4 * r4 + j] = a[j][0];
+    } else {
+        out[(lane < kH ? kOffB2 : kOffW3) + c0] = a[0][0];
+        if (lane == 0) {
+            out[kOffB3] = a[1][0];
+            if (chunk == 0) L.sq[0] = loss;
+        }
+    }
+    __syncthreads();
+    float *row = partial + (int64_t)blockIdx.x * (kNParam + 1);
+    for (int p = tid; p <= kNParam; p += kGradWG) {
+        float r = 0.f;
+        if (p == kNParam)
+            r = L.sq[0];
+        else if (p >= kOffW1)
+            for (int c = 0; c < 4; ++c) r += red[c][p];
+        row[p] = r;
     }
 }
 
-// grad[p] = sum over workgroups (fixed order: eight interleaved sums per
-// parameter, then those in turn); loss = sum of squares / n.  32 parameters x
-// 8 row groups per workgroup; one thread per parameter over all rows took 16
-// us for 64 rows.
-constexpr int kRedCols = 32, kRedRows = kWG / kRedCols;
-__global__ __launch_bounds__(kWG) void mlp_grad_reduce_kernel(const float *__restrict__ partial, int nwg, int64_t n,
+// grad[p] = sum over workgroups in turn; loss = sum of squares / n.  A
+// workgroup takes 32 parameters and brings 256 rows of theirs into LDS at a
+// time, from where one thread each adds them up: the additions wait for one
+// another, the loads do not.
+constexpr int kRedCols = 32, kRedRows = 256;
+__global__ __launch_bounds__(kWG) void mlp_grad_reduce_kernel(const float *__restrict__ partial, int64_t nwg, int64_t n,
                                                                float *__restrict__ grad, float *__restrict__ loss)
 {
     __shared__ float s[kRedRows][kRedCols];
     const int c = threadIdx.x % kRedCols, g = threadIdx.x / kRedCols;
     const int p = blockIdx.x * kRedCols + c;
     float a = 0.f;
-    if (p <= kNParam)
-        for (int w = g; w < nwg; w += kRedRows) a += partial[(int64_t)w * (kNParam + 1) + p];
-    s[g][c] = a;
-    __syncthreads();
+    for (int64_t w0 = 0; w0 < nwg; w0 += kRedRows) {
+        const int rows = nwg - w0 < kRedRows ? (int)(nwg - w0) : kRedRows;
+        if (p <= kNParam)
+#pragma unroll 8
+            for (int w = g; w < rows; w += kWG / kRedCols) s[w][c] = partial[(w0 + w) * (kNParam + 1) + p];
+        __syncthreads();
+        if (g == 0 && p <= kNParam)
+#pragma unroll 16
+            for (int w = 0; w < rows; ++w) a += s[w][c];
+        __syncthreads();
+    }
     if (g != 0 || p > kNParam) return;
-    a = 0.f;
-    for (int k = 0; k < kRedRows; ++k) a += s[k][c];
     if (p < kNParam)
         grad[p] = a;
     else
@@ -419,13 +369,12 @@ size_t mlp_grad_workspace_bytes(int64_t n)
 hipError_t launch_mlp_grad(const float *P, const float *raw, const float *target, int64_t n, float inv_scale,
                            float *grad, float *loss, float *work, hipStream_t st)
 {
-    // one workgroup per 256 samples (a row of the workspace each), up to two per CU
-    const int64_t nwg = std::min<int64_t>((n + kGradWaves * kTileS - 1) / (kGradWaves * kTileS), kMaxGradWG);
+    const int64_t nwg = (n + kWG - 1) / kWG;
     hipLaunchKernelGGL(mlp_grad_kernel, dim3((int)nwg), dim3(kGradWG), 0, st, P, raw, target, n, inv_scale, work);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(mlp_grad_reduce_kernel, dim3((kNParam + 1 + kRedCols - 1) / kRedCols), dim3(kWG), 0, st, work,
-                       (int)nwg, n, grad, loss);
+                       nwg, n, grad, loss);
     return hipGetLastError();
 }
 
