@@ -132,7 +132,7 @@ public:
             }
             {
                 std::lock_guard<std::mutex> lk(mu_);
-                piece_[k] = Piece{static_cast<char *>(dev) + o, m, (int)((m + kPart - 1) / kPart), true};
+                piece_[k] = Piece{static_cast<char *>(dev) + o, m, (int)((m + kPart - 1) / kPart), true, false};
                 for (size_t q = 0; q < m; q += kPart)
                     queue_.push_back(Part{static_cast<char *>(host) + o + q, q, std::min(kPart, m - q), k});
             }
@@ -159,6 +159,7 @@ private:
         size_t n;
         int left;  // parts not yet copied
         bool busy;
+        bool ready;  // to the device: all parts copied, not yet enqueued
     };
     struct Part {
         char *host;
@@ -181,18 +182,41 @@ private:
             want_ = 0;  // the threads there are and the caller's own do the rest
         }
     }
-    // Waits until slot k holds no unfinished piece, working on parts
-    // meanwhile; false after an error.
+    // Waits until slot k holds no unfinished piece, working on parts and
+    // enqueuing finished ones meanwhile; false after an error.
     bool free_slot(int k)
     {
         std::unique_lock<std::mutex> lk(mu_);
-        while (piece_[k].busy) {
-            if (!queue_.empty())
+        for (;;) {
+            if (ready_ > 0)
+                send_ready(lk);
+            else if (!piece_[k].busy)
+                return err_ == hipSuccess;
+            else if (!queue_.empty())
                 run_one(lk);
             else
                 cv_.wait(lk);
         }
-        return err_ == hipSuccess;
+    }
+    // Enqueues the pieces that are whole in their buffers.  Only the thread
+    // that makes the transfer does this: the stream may be the calling
+    // thread's own (hipStreamPerThread), another one in a copying thread.
+    void send_ready(std::unique_lock<std::mutex> &lk)
+    {
+        for (int k = 0; k < PinnedRing::kSlots; ++k) {
+            Piece &w = piece_[k];
+            if (!w.ready) continue;
+            w.ready = false;
+            --ready_;
+            if (err_ == hipSuccess) {
+                lk.unlock();
+                hipError_t e = hipMemcpyAsync(w.dev, ring_.slot(k), w.n, hipMemcpyHostToDevice, st_);
+                if (e == hipSuccess) e = hipEventRecord(ring_.event(k), st_);
+                lk.lock();
+                if (e != hipSuccess && err_ == hipSuccess) err_ = e;
+            }
+            w.busy = false;
+        }
     }
     // Takes the oldest part and copies it with the lock released.
     void run_one(std::unique_lock<std::mutex> &lk)
@@ -214,14 +238,12 @@ private:
         if (e != hipSuccess && err_ == hipSuccess) err_ = e;
         Piece &w = piece_[p.slot];
         if (--w.left > 0) return;
-        if (!to_host_ && err_ == hipSuccess) {  // the whole piece is in the buffer
-            lk.unlock();
-            e = hipMemcpyAsync(w.dev, ring_.slot(p.slot), w.n, hipMemcpyHostToDevice, st_);
-            if (e == hipSuccess) e = hipEventRecord(ring_.event(p.slot), st_);
-            lk.lock();
-            if (e != hipSuccess && err_ == hipSuccess) err_ = e;
+        if (to_host_) {
+            w.busy = false;
+        } else {
+            w.ready = true;
+            ++ready_;
         }
-        w.busy = false;
         cv_.notify_all();
     }
     // Maps the pages of a destination in one call: 9 GB/s per thread of 4 KiB
@@ -245,7 +267,7 @@ private:
     std::deque<Part> queue_;
     Piece piece_[PinnedRing::kSlots] = {};
     bool done_ = false;
-    int next_ = 0;
+    int next_ = 0, ready_ = 0;
     hipError_t err_ = hipSuccess;
     std::vector<std::thread> workers_;
 };

@@ -1,0 +1,86 @@
+// Host transfers (transfer.hpp) on the CPU, against stand-ins for the runtime
+// calls they make: "device" memory is host memory, copies are done at once,
+// and each stand-in checks how it is called.  One check per command-line name.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <atomic>
+#include <thread>
+
+#include "transfer.hpp"
+
+static void bad(const char *what)
+{
+    fprintf(stderr, "%s\n", what);
+    exit(1);
+}
+
+static std::atomic<int> n_copies{0};
+static const std::thread::id main_thread = std::this_thread::get_id();
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostFree(void *p) { return free(p), hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return *e = (hipEvent_t)malloc(1), hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { return free(e), hipSuccess; }
+// a copying thread is delayed now and then, so that pieces end out of order
+hipError_t hipEventSynchronize(hipEvent_t)
+{
+    static std::atomic<unsigned> k{0};
+    if (++k % 5 == 0) std::this_thread::sleep_for(std::chrono::microseconds(50));
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t, hipStream_t)
+{
+    if (std::this_thread::get_id() != main_thread) bad("an event is recorded by a copying thread");
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t)
+{
+    if (std::this_thread::get_id() != main_thread) bad("a copy is enqueued by a copying thread");
+    ++n_copies;
+    return memcpy(dst, src, n), hipSuccess;
+}
+}
+
+using namespace wlb;
+
+// Arrays of sizes around the pieces and parts, in both directions and through
+// one ring, arrive whole.
+static void round_trips()
+{
+    PinnedRing ring;
+    const size_t mb = (size_t)1 << 20;
+    const size_t sizes[] = {1, 4095, 512 << 10, (512 << 10) + 1, 4 * mb - 8, 4 * mb, 4 * mb + 1, 63 * mb + 5};
+    for (int k = 0; k < 4; ++k)
+        for (bool to_host : {true, false}) {
+            HostCopy c(ring, to_host, nullptr, 140 * mb);
+            char *src[8], *dst[8];
+            for (int i = 0; i < 8; ++i) {
+                src[i] = (char *)malloc(sizes[i]);
+                dst[i] = (char *)malloc(sizes[i]);
+                for (size_t o = 0; o < sizes[i]; o += 97) src[i][o] = (char)(o * 31 + i + k);
+                memset(dst[i], 0x55, sizes[i]);
+                if (c.add(to_host ? dst[i] : src[i], to_host ? src[i] : dst[i], sizes[i]) != hipSuccess) bad("add");
+                if (i == 4 && c.flush() != hipSuccess) bad("flush");
+            }
+            if (c.flush() != hipSuccess) bad("flush");
+            for (int i = 0; i < 8; ++i) {
+                if (memcmp(src[i], dst[i], sizes[i])) bad("contents");
+                free(src[i]);
+                free(dst[i]);
+            }
+        }
+}
+
+int main(int argc, char **argv)
+{
+    const char *what = argc > 1 ? argv[1] : "";
+    if (!strcmp(what, "round_trips")) round_trips();
+    else bad("unknown check");
+    puts("ok");
+}

@@ -1,0 +1,34 @@
+"""The host side of the transfers between caller-owned arrays and the device
+(transfer.hpp) on the CPU, with stand-ins for the runtime calls."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_1909_13772_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    if shutil.which("g++") is None or not os.path.exists(os.path.join(ROCM, "include/hip/hip_runtime.h")):
+        pytest.skip("g++ or the HIP headers are not available")
+    exe = str(tmp_path_factory.mktemp("host_copy") / "host_copy_check")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-pthread", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROCM, "include"),
+           "-I" + CSRC, os.path.join(HERE, "host_copy_check.cpp"), "-o", exe]
+    b = subprocess.run(cmd, capture_output=True, text=True)
+    assert b.returncode == 0, b.stderr[-3000:]
+
+    def run(what):
+        r = subprocess.run([exe, what], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and r.stdout.strip() == "ok", (what, r.stdout[-500:], r.stderr[-2000:])
+
+    return run
+
+
+def test_copies_are_enqueued_by_the_calling_thread(check):
+    """The bound stream may be the calling thread's own: nothing is enqueued
+    from the copying threads, and every array arrives whole."""
+    check("round_trips")
