@@ -19,11 +19,8 @@
 #include <algorithm>
 #include <condition_variable>
 #include <cstring>
-#include <deque>
 #include <mutex>
-#include <system_error>
 #include <thread>
-#include <vector>
 
 namespace wlb {
 
@@ -35,7 +32,7 @@ public:
     static constexpr size_t kChunk = (size_t)4 << 20;
     ~PinnedRing()
     {
-        for (hipEvent_t e : ev_) (void)hipEventDestroy(e);
+        for (int k = 0; k < n_ev_; ++k) (void)hipEventDestroy(ev_[k]);
         if (base_) (void)hipHostFree(base_);
         if (small_) (void)hipHostFree(small_);
     }
@@ -51,14 +48,11 @@ public:
             if (!base_) return false;
             chunk_ = chunk;
         }
-        while ((int)ev_.size() < kSlots) {
-            hipEvent_t e;
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        for (; n_ev_ < kSlots; ++n_ev_)
+            if (hipEventCreateWithFlags(&ev_[n_ev_], hipEventDisableTiming) != hipSuccess) {
                 (void)hipGetLastError();
                 return false;
             }
-            ev_.push_back(e);
-        }
         return true;
     }
     char *slot(int k) const { return static_cast<char *>(base_) + (size_t)k * chunk_; }
@@ -80,7 +74,8 @@ private:
     }
     void *base_ = nullptr, *small_ = nullptr;
     size_t chunk_ = 0;
-    std::vector<hipEvent_t> ev_;
+    hipEvent_t ev_[kSlots];
+    int n_ev_ = 0;
 };
 
 // One transfer of about `total` bytes in one direction on one stream, as any
@@ -89,7 +84,9 @@ private:
 // take a quarter of their size), and a piece is copied on the host in parts
 // of 512 KB by whichever thread is free.  Device-side order is the stream's: a
 // kernel launched before add() has finished when its pieces are read, and one
-// launched after flush() sees every piece written.
+// launched after flush() sees every piece written.  Nothing here throws, for
+// the C entry points that use it: its lists have a fixed size, and threads
+// that cannot be had are done without.
 class HostCopy {
 public:
     HostCopy(PinnedRing &ring, bool to_host, hipStream_t st, size_t total) : ring_(ring), to_host_(to_host), st_(st)
@@ -103,7 +100,7 @@ public:
         if (!pinned_) return;
         cpu_set_t cs;
         const int cpus = sched_getaffinity(0, sizeof cs, &cs) == 0 ? CPU_COUNT(&cs) : 1;
-        want_ = std::min((int)std::min<size_t>(7, total >> 20), cpus - 1);  // one more thread per MB
+        want_ = std::min((int)std::min<size_t>(kWorkers, total >> 20), cpus - 1);  // one more thread per MB
         (void)hipGetDevice(&dev_);
     }
     ~HostCopy()
@@ -113,7 +110,7 @@ public:
             done_ = true;
         }
         cv_.notify_all();
-        for (std::thread &t : workers_) t.join();
+        for (int k = 0; k < n_workers_; ++k) workers_[k].join();
     }
     hipError_t add(void *host, void *dev, size_t n)
     {
@@ -134,11 +131,11 @@ public:
                 std::lock_guard<std::mutex> lk(mu_);
                 piece_[k] = Piece{static_cast<char *>(dev) + o, m, (int)((m + kPart - 1) / kPart), true, false};
                 for (size_t q = 0; q < m; q += kPart)
-                    queue_.push_back(Part{static_cast<char *>(host) + o + q, q, std::min(kPart, m - q), k});
+                    queue_[(head_ + n_queued_++) % kParts] = Part{static_cast<char *>(host) + o + q, q, std::min(kPart, m - q), k};
             }
             cv_.notify_all();
             // threads start while the link is busy with what is under way
-            if ((int)workers_.size() < want_) spawn();
+            if (n_workers_ < want_) spawn();
         }
         return hipSuccess;
     }
@@ -154,6 +151,7 @@ public:
 
 private:
     static constexpr size_t kPart = (size_t)512 << 10;
+    static constexpr int kWorkers = 7, kParts = PinnedRing::kSlots * (int)(PinnedRing::kChunk / kPart);
     struct Piece {
         char *dev;
         size_t n;
@@ -169,16 +167,17 @@ private:
     void spawn()
     {
         try {
-            workers_.emplace_back([this] {
+            workers_[n_workers_] = std::thread([this] {
                 (void)hipSetDevice(dev_);
                 std::unique_lock<std::mutex> lk(mu_);
                 for (;;) {
-                    cv_.wait(lk, [this] { return done_ || !queue_.empty(); });
-                    if (queue_.empty()) return;
+                    cv_.wait(lk, [this] { return done_ || n_queued_ > 0; });
+                    if (n_queued_ == 0) return;
                     run_one(lk);
                 }
             });
-        } catch (const std::system_error &) {
+            ++n_workers_;
+        } catch (...) {
             want_ = 0;  // the threads there are and the caller's own do the rest
         }
     }
@@ -192,7 +191,7 @@ private:
                 send_ready(lk);
             else if (!piece_[k].busy)
                 return err_ == hipSuccess;
-            else if (!queue_.empty())
+            else if (n_queued_ > 0)
                 run_one(lk);
             else
                 cv_.wait(lk);
@@ -221,8 +220,9 @@ private:
     // Takes the oldest part and copies it with the lock released.
     void run_one(std::unique_lock<std::mutex> &lk)
     {
-        const Part p = queue_.front();
-        queue_.pop_front();
+        const Part p = queue_[head_];
+        head_ = (head_ + 1) % kParts;
+        --n_queued_;
         lk.unlock();
         hipError_t e;
         if (to_host_) {
@@ -264,12 +264,14 @@ private:
     int want_ = 0, dev_ = 0;
     std::mutex mu_;
     std::condition_variable cv_;
-    std::deque<Part> queue_;
+    Part queue_[kParts];  // parts of the busy pieces not yet taken, oldest at head_
+    int head_ = 0, n_queued_ = 0;
     Piece piece_[PinnedRing::kSlots] = {};
     bool done_ = false;
     int next_ = 0, ready_ = 0;
     hipError_t err_ = hipSuccess;
-    std::vector<std::thread> workers_;
+    std::thread workers_[kWorkers];
+    int n_workers_ = 0;
 };
 
 }  // namespace wlb

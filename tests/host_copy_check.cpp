@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <new>
 #include <thread>
 
 #include "transfer.hpp"
@@ -15,6 +16,16 @@ static void bad(const char *what)
     fprintf(stderr, "%s\n", what);
     exit(1);
 }
+
+static std::atomic<bool> no_memory{false};
+void *operator new(size_t n)
+{
+    void *p = no_memory ? nullptr : malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 static std::atomic<int> n_copies{0};
 static const std::thread::id main_thread = std::this_thread::get_id();
@@ -81,6 +92,10 @@ int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "round_trips")) round_trips();
+    else if (!strcmp(what, "no_memory")) {
+        no_memory = true;
+        round_trips();
+    }
     else bad("unknown check");
     puts("ok");
 }

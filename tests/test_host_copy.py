@@ -32,3 +32,9 @@ def test_copies_are_enqueued_by_the_calling_thread(check):
     """The bound stream may be the calling thread's own: nothing is enqueued
     from the copying threads, and every array arrives whole."""
     check("round_trips")
+
+
+def test_no_exception_without_memory(check):
+    """With every host allocation failing (the lists, the threads) nothing is
+    thrown through the C entry points: the calling thread does the work."""
+    check("no_memory")
