@@ -768,7 +768,7 @@ struct Sums {
 };
 Sums sums_target(wlb_blocks *h)
 {
-    if (double *p = h->ring.sums()) return Sums{p, true};
+    if (double *p = h->ring.sums(h->stream)) return Sums{p, true};
     return Sums{reinterpret_cast<double *>(h->arena + h->off_totals), false};
 }
 // Waits for the stream and hands the sums out.
@@ -1594,10 +1594,10 @@ int wlb_blocks_bind(wlb_blocks_t h, void *arena, size_t bytes, void *stream)
     // pinned buffers of the field and population transfers (0.2 ms; the first
     // transfer would pay for them otherwise), failing which copies go direct
     if (small_fields(h))
-        (void)h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1);
+        (void)h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1, h->stream);
     else
-        (void)h->ring.reserve(PinnedRing::kChunk);
-    (void)h->ring.sums();
+        (void)h->ring.reserve(PinnedRing::kChunk, h->stream);
+    (void)h->ring.sums(h->stream);
     if (h->overlap) {
         int rc = ensure_stream2(h);
         if (rc) return rc;
@@ -1859,7 +1859,7 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
     double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
     // small fields are written straight into pinned host memory by the kernel
     // (32^3: 1 MB; four copies of 256 KB cost 14 us each)
-    const bool direct = whole && small_fields(h) && h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1);
+    const bool direct = whole && small_fields(h) && h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1, h->stream);
     if (direct) stage = reinterpret_cast<double *>(h->ring.slot(0));
     const Sums tot = sums_target(h);
     auto fields = [&](int z0, int z1) -> int {

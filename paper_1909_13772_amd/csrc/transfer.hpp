@@ -24,6 +24,29 @@
 
 namespace wlb {
 
+// Makes the device of a stream the current one: events have to be created on
+// the device of the stream that records them, which need not be the caller's
+// current one.
+class OnDeviceOf {
+public:
+    explicit OnDeviceOf(hipStream_t st)
+    {
+        if (hipGetDevice(&before_) != hipSuccess || hipStreamGetDevice(st, &dev_) != hipSuccess) {
+            (void)hipGetLastError();
+            before_ = dev_ = -1;
+        }
+        if (dev_ != before_) (void)hipSetDevice(dev_);
+    }
+    ~OnDeviceOf()
+    {
+        if (dev_ != before_) (void)hipSetDevice(before_);
+    }
+    int device() const { return dev_; }
+
+private:
+    int before_ = -1, dev_ = -1;
+};
+
 // Pinned buffers of one handle, allocated at its first transfer and released
 // with it (kSlots x kChunk = 40 MB at most).
 class PinnedRing {
@@ -32,14 +55,15 @@ public:
     static constexpr size_t kChunk = (size_t)4 << 20;
     ~PinnedRing()
     {
-        for (int k = 0; k < n_ev_; ++k) (void)hipEventDestroy(ev_[k]);
+        drop_events();
         if (base_) (void)hipHostFree(base_);
         if (small_) (void)hipHostFree(small_);
     }
-    // Room for kSlots pieces of `chunk` bytes, one after the other; false
-    // without pinned memory.
-    bool reserve(size_t chunk)
+    // Room for kSlots pieces of `chunk` bytes, one after the other, for
+    // transfers on `st`; false without pinned memory.
+    bool reserve(size_t chunk, hipStream_t st)
     {
+        const OnDeviceOf on(st);
         chunk = (chunk + 4095) & ~(size_t)4095;
         if (chunk > chunk_) {
             if (base_) (void)hipHostFree(base_);
@@ -48,6 +72,8 @@ public:
             if (!base_) return false;
             chunk_ = chunk;
         }
+        if (on.device() != dev_) drop_events();
+        dev_ = on.device();
         for (; n_ev_ < kSlots; ++n_ev_)
             if (hipEventCreateWithFlags(&ev_[n_ev_], hipEventDisableTiming) != hipSuccess) {
                 (void)hipGetLastError();
@@ -58,13 +84,20 @@ public:
     char *slot(int k) const { return static_cast<char *>(base_) + (size_t)k * chunk_; }
     hipEvent_t event(int k) const { return ev_[k]; }
     // A few words that kernels write their sums to; null without pinned memory.
-    double *sums()
+    double *sums(hipStream_t st)
     {
-        if (!small_) small_ = pinned(4096);
+        if (!small_) {
+            const OnDeviceOf on(st);
+            small_ = pinned(4096);
+        }
         return static_cast<double *>(small_);
     }
 
 private:
+    void drop_events()
+    {
+        for (; n_ev_ > 0; --n_ev_) (void)hipEventDestroy(ev_[n_ev_ - 1]);
+    }
     static void *pinned(size_t n)
     {
         void *p = nullptr;
@@ -75,7 +108,7 @@ private:
     void *base_ = nullptr, *small_ = nullptr;
     size_t chunk_ = 0;
     hipEvent_t ev_[kSlots];
-    int n_ev_ = 0;
+    int n_ev_ = 0, dev_ = -1;  // events, and the device they belong to
 };
 
 // One transfer of about `total` bytes in one direction on one stream, as any
@@ -96,12 +129,11 @@ public:
         if (!to_host && total < ((size_t)128 << 20)) return;
         chunk_ = std::min(PinnedRing::kChunk, std::max<size_t>((size_t)256 << 10, total / 4));
         chunk_ = (chunk_ + 4095) & ~(size_t)4095;
-        pinned_ = ring.reserve(chunk_);
+        pinned_ = ring.reserve(chunk_, st);
         if (!pinned_) return;
         cpu_set_t cs;
         const int cpus = sched_getaffinity(0, sizeof cs, &cs) == 0 ? CPU_COUNT(&cs) : 1;
         want_ = std::min((int)std::min<size_t>(kWorkers, total >> 20), cpus - 1);  // one more thread per MB
-        (void)hipGetDevice(&dev_);
     }
     ~HostCopy()
     {
@@ -168,7 +200,6 @@ private:
     {
         try {
             workers_[n_workers_] = std::thread([this] {
-                (void)hipSetDevice(dev_);
                 std::unique_lock<std::mutex> lk(mu_);
                 for (;;) {
                     cv_.wait(lk, [this] { return done_ || n_queued_ > 0; });
@@ -261,7 +292,7 @@ private:
     hipStream_t st_;
     size_t chunk_ = 0;
     bool pinned_ = false;
-    int want_ = 0, dev_ = 0;
+    int want_ = 0;
     std::mutex mu_;
     std::condition_variable cv_;
     Part queue_[kParts];  // parts of the busy pieces not yet taken, oldest at head_

@@ -30,13 +30,21 @@ void operator delete(void *p, size_t) noexcept { free(p); }
 static std::atomic<int> n_copies{0};
 static const std::thread::id main_thread = std::this_thread::get_id();
 
+// two devices; a stream's handle is 1000 times its device (0: the null stream)
+static thread_local int device = 0;
+static int device_of(hipStream_t st) { return st ? (int)((uintptr_t)st / 1000) : device; }
+struct Event {
+    int device;
+};
+
 extern "C" {
-hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDevice(int *d) { return *d = device, hipSuccess; }
+hipError_t hipSetDevice(int d) { return device = d, hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t st, hipDevice_t *d) { return *d = device_of(st), hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostFree(void *p) { return free(p), hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return *e = (hipEvent_t)malloc(1), hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return *e = (hipEvent_t)malloc(sizeof(Event)), ((Event *)*e)->device = device, hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { return free(e), hipSuccess; }
 // a copying thread is delayed now and then, so that pieces end out of order
 hipError_t hipEventSynchronize(hipEvent_t)
@@ -45,8 +53,9 @@ hipError_t hipEventSynchronize(hipEvent_t)
     if (++k % 5 == 0) std::this_thread::sleep_for(std::chrono::microseconds(50));
     return hipSuccess;
 }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t)
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t st)
 {
+    if (((Event *)e)->device != device_of(st)) return hipErrorInvalidHandle;
     if (std::this_thread::get_id() != main_thread) bad("an event is recorded by a copying thread");
     return hipSuccess;
 }
@@ -62,14 +71,13 @@ using namespace wlb;
 
 // Arrays of sizes around the pieces and parts, in both directions and through
 // one ring, arrive whole.
-static void round_trips()
+static void round_trips(PinnedRing &ring, hipStream_t st)
 {
-    PinnedRing ring;
     const size_t mb = (size_t)1 << 20;
     const size_t sizes[] = {1, 4095, 512 << 10, (512 << 10) + 1, 4 * mb - 8, 4 * mb, 4 * mb + 1, 63 * mb + 5};
     for (int k = 0; k < 4; ++k)
         for (bool to_host : {true, false}) {
-            HostCopy c(ring, to_host, nullptr, 140 * mb);
+            HostCopy c(ring, to_host, st, 140 * mb);
             char *src[8], *dst[8];
             for (int i = 0; i < 8; ++i) {
                 src[i] = (char *)malloc(sizes[i]);
@@ -91,10 +99,17 @@ static void round_trips()
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
-    if (!strcmp(what, "round_trips")) round_trips();
+    PinnedRing ring;
+    if (!strcmp(what, "round_trips")) round_trips(ring, nullptr);
     else if (!strcmp(what, "no_memory")) {
         no_memory = true;
-        round_trips();
+        round_trips(ring, nullptr);
+    }
+    else if (!strcmp(what, "devices")) {
+        for (int d : {1, 0, 1}) {
+            round_trips(ring, (hipStream_t)(uintptr_t)(1000 * d + 1));
+            if (device != 0) bad("the caller's device has changed");
+        }
     }
     else bad("unknown check");
     puts("ok");

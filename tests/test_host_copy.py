@@ -38,3 +38,9 @@ def test_no_exception_without_memory(check):
     """With every host allocation failing (the lists, the threads) nothing is
     thrown through the C entry points: the calling thread does the work."""
     check("no_memory")
+
+
+def test_streams_of_another_device(check):
+    """The caller's current device need not be the bound stream's: events
+    belong to the stream's device, and the current one stays."""
+    check("devices")
