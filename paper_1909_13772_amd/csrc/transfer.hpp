@@ -115,7 +115,9 @@ private:
 // number of arrays.  An array goes over the link in pieces of up to 4 MB
 // (45-54 GB/s; a piece costs some 9 us beyond its bytes, so small transfers
 // take a quarter of their size), and a piece is copied on the host in parts
-// of 512 KB by whichever thread is free.  Device-side order is the stream's: a
+// of 512 KB by whichever thread is free.  Arrays in memory that the runtime
+// knows are copied without buffers.  They are whole, like the others after
+// flush(), once the stream has been waited for.  Device-side order is the stream's: a
 // kernel launched before add() has finished when its pieces are read, and one
 // launched after flush() sees every piece written.  Nothing here throws, for
 // the C entry points that use it: its lists have a fixed size, and threads
@@ -144,9 +146,20 @@ public:
         cv_.notify_all();
         for (int k = 0; k < n_workers_; ++k) workers_[k].join();
     }
+    // Memory the runtime knows (pinned or registered by the caller, managed,
+    // device): the copy engine reads and writes it itself.
+    static bool mapped(const void *p)
+    {
+        hipPointerAttribute_t a;
+        if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type != hipMemoryTypeUnregistered;
+        (void)hipGetLastError();
+        return false;
+    }
     hipError_t add(void *host, void *dev, size_t n)
     {
-        if (!pinned_)
+        // through the buffers pinned arrays would only be slower (populations
+        // of 100^3, 152 MB: 3.7 ms against 3.2; density of 64^3: 163 us against 64)
+        if (!pinned_ || mapped(host))
             return to_host_ ? hipMemcpyAsync(host, dev, n, hipMemcpyDeviceToHost, st_)
                             : hipMemcpyAsync(dev, host, n, hipMemcpyHostToDevice, st_);
         for (size_t o = 0; o < n; o += chunk_) {

@@ -27,7 +27,12 @@ void *operator new(size_t n)
 void operator delete(void *p) noexcept { free(p); }
 void operator delete(void *p, size_t) noexcept { free(p); }
 
-static std::atomic<int> n_copies{0};
+// memory known to the runtime
+static char *known = nullptr;
+static size_t known_bytes = 0;
+static bool is_known(const void *p) { return known && (const char *)p >= known && (const char *)p < known + known_bytes; }
+
+static std::atomic<int> n_copies{0}, n_known{0};
 static const std::thread::id main_thread = std::this_thread::get_id();
 
 // two devices; a stream's handle is 1000 times its device (0: the null stream)
@@ -59,8 +64,15 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t st)
     if (std::this_thread::get_id() != main_thread) bad("an event is recorded by a copying thread");
     return hipSuccess;
 }
-hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t)
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
 {
+    memset(a, 0, sizeof *a);
+    a->type = is_known(p) ? hipMemoryTypeHost : hipMemoryTypeUnregistered;
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind kind, hipStream_t)
+{
+    n_known += is_known(kind == hipMemcpyDeviceToHost ? dst : src);
     if (std::this_thread::get_id() != main_thread) bad("a copy is enqueued by a copying thread");
     ++n_copies;
     return memcpy(dst, src, n), hipSuccess;
@@ -96,6 +108,28 @@ static void round_trips(PinnedRing &ring, hipStream_t st)
         }
 }
 
+// An array that the runtime knows is copied as a whole from or to its place,
+// whatever the others of the transfer are.
+static void known_memory()
+{
+    PinnedRing ring;
+    const size_t n = ((size_t)9 << 20) + 3;
+    char *dev = (char *)malloc(n), *other = (char *)malloc(n);
+    known = (char *)calloc(n, 1);
+    known_bytes = n;
+    for (bool to_host : {true, false}) {
+        n_copies = n_known = 0;
+        memset(to_host ? dev : known, to_host ? 1 : 2, n);
+        HostCopy c(ring, to_host, nullptr, (size_t)140 << 20);
+        if (c.add(known, dev, n) != hipSuccess || c.flush() != hipSuccess) bad("add");
+        if (n_copies != 1 || n_known != 1) bad("a known array is copied through buffers");
+        if (memcmp(known, dev, n)) bad("contents");
+        if (c.add(other, dev, n) != hipSuccess || c.flush() != hipSuccess) bad("add");
+        if (n_copies != 4 || n_known != 1) bad("an ordinary array is not copied through buffers");
+        if (memcmp(other, dev, n)) bad("contents");
+    }
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
@@ -111,6 +145,7 @@ int main(int argc, char **argv)
             if (device != 0) bad("the caller's device has changed");
         }
     }
+    else if (!strcmp(what, "known_memory")) known_memory();
     else bad("unknown check");
     puts("ok");
 }

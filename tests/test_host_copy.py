@@ -44,3 +44,8 @@ def test_streams_of_another_device(check):
     """The caller's current device need not be the bound stream's: events
     belong to the stream's device, and the current one stays."""
     check("devices")
+
+
+def test_pinned_arrays_are_copied_in_place(check):
+    """Arrays that the runtime knows go over the link as they are."""
+    check("known_memory")
