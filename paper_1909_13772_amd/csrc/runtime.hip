@@ -760,6 +760,21 @@ int capture_graph(wlb_blocks *h, int k)
 size_t field_bytes(const wlb_blocks *h) { return 4 * sizeof(double) * (size_t)h->ncells; }
 bool small_fields(const wlb_blocks *h) { return field_bytes(h) <= ((size_t)2 << 20); }
 
+// Elements [first, first + S) of `count` arrays of N elements each, against
+// `count` stretches of S elements in the staging area.  Whole arrays are one
+// stretch on both sides and go as one (populations of 16^3, 0.6 MB: 19 copies
+// take 230 us), unless they are larger and the runtime copies them from or to
+// pageable memory, where it is faster in parts (velocity of 48^3: three copies
+// 149 us, one 168).
+hipError_t add_arrays(HostCopy &c, double *host, double *stage, int count, int64_t N, int64_t first, int64_t S)
+{
+    const bool one = c.buffered() || S * sizeof(double) <= ((size_t)256 << 10) || HostCopy::mapped(host);
+    if (S == N && one) return c.add(host, stage, count * N * sizeof(double));
+    hipError_t e = hipSuccess;
+    for (int a = 0; a < count && e == hipSuccess; ++a) e = c.add(host + a * N + first, stage + a * S, S * sizeof(double));
+    return e;
+}
+
 // Where the last pass of a reduction writes its eight sums: pinned host
 // memory, which is the caller's after the next synchronisation, or the arena.
 struct Sums {
@@ -791,7 +806,6 @@ int compute_totals(wlb_blocks *h, double *host8)
     m.swapped = h->parity;
     m.z0 = 0;
     m.z1 = 0;
-    m.out = nullptr;
     m.partials = partials_of(h);
     HIPCHK(moments_dispatch(h, m, aux_grid(h)));
     const Sums tot = sums_target(h);
@@ -834,8 +848,7 @@ int do_init_state(wlb_blocks *h, const double *rho, const double *u)
         const int z1 = std::min(h->dom[2], z0 + kz);
         const int64_t S = (int64_t)(z1 - z0) * plane;
         HIPCHK(up.add(const_cast<double *>(rho) + z0 * plane, stage, S * sizeof(double)));
-        for (int a = 0; a < 3; ++a)
-            HIPCHK(up.add(const_cast<double *>(u) + a * N + z0 * plane, stage + (1 + a) * S, S * sizeof(double)));
+        HIPCHK(add_arrays(up, const_cast<double *>(u), stage + S, 3, N, z0 * plane, S));
         HIPCHK(up.flush());
         HIPCHK(init_dispatch(h, stage, z0, z1, aux_grid(h)));
     }
@@ -1859,7 +1872,7 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
     double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
     // small fields are written straight into pinned host memory by the kernel
     // (32^3: 1 MB; four copies of 256 KB cost 14 us each), into pinned arrays
-    // of the caller's by copies from 1 MB on (40^3: 115 us against 121)
+    // of the caller's by copies from 1 MB on (40^3: 115 us against 121).
     const bool mapped = (!rho || HostCopy::mapped(rho)) && (!u || HostCopy::mapped(u));
     const bool direct = whole && small_fields(h) && !(mapped && field_bytes(h) > ((size_t)1 << 20)) &&
                         h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1, h->stream);
@@ -1871,7 +1884,8 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
         m.swapped = h->parity;
         m.z0 = z0;
         m.z1 = z1;
-        m.out = stage;
+        if (rho) m.rho = stage;
+        if (u) m.u = stage + (int64_t)(z1 - z0) * plane;
         m.partials = totals && whole ? partials_of(h) : nullptr;
         HIPCHK(moments_dispatch(h, m, aux_grid(h)));
         if (m.partials) HIPCHK(launch_reduce_totals(m.partials, (int)h->tiles.size(), groups_of(h), tot.at, h->stream));
@@ -1888,9 +1902,7 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
             const int rc = fields(z0, z1);
             if (rc) return rc;
             if (rho) HIPCHK(down.add(rho + z0 * plane, stage, S * sizeof(double)));
-            if (u)
-                for (int a = 0; a < 3; ++a)
-                    HIPCHK(down.add(u + a * N + z0 * plane, stage + (1 + a) * S, S * sizeof(double)));
+            if (u) HIPCHK(add_arrays(down, u, stage + S, 3, N, z0 * plane, S));
         }
         HIPCHK(down.flush());
     }
@@ -1965,7 +1977,7 @@ static int pdfs_io(wlb_blocks_t h, double *d, bool to_dev)
         const int z1 = std::min(h->dom[2], z0 + kz);
         const int64_t S = (int64_t)(z1 - z0) * plane;
         if (!to_dev) HIPCHK(pdfs_dispatch(h, stage, z0, z1, false, h->parity == 1, aux_grid(h)));
-        for (int i = 0; i < h->q; ++i) HIPCHK(link.add(d + i * N + z0 * plane, stage + i * S, S * sizeof(double)));
+        HIPCHK(add_arrays(link, d, stage, h->q, N, z0 * plane, S));
         if (to_dev) {
             HIPCHK(link.flush());
             HIPCHK(pdfs_dispatch(h, stage, z0, z1, true, false, aux_grid(h)));

@@ -2089,13 +2089,12 @@ __global__ __launch_bounds__(kWG) void moments_kernel(const MomArgs ma)
                 acc[5] = sqrt(uu);
                 acc[6] = 1.0;
             }
-            if (ma.out && gz >= ma.z0 && gz < ma.z1) {
+            if (gz >= ma.z0 && gz < ma.z1) {
                 const int64_t S = (int64_t)(ma.z1 - ma.z0) * a.dom[1] * a.dom[0];
                 const int64_t k = ((int64_t)(gz - ma.z0) * a.dom[1] + gy) * a.dom[0] + gx;
-                ma.out[k] = rho;
-                ma.out[S + k] = u[0];
-                ma.out[2 * S + k] = u[1];
-                ma.out[3 * S + k] = u[2];
+                if (ma.rho) ma.rho[k] = rho;
+                if (ma.u)
+                    for (int d = 0; d < 3; ++d) ma.u[d * S + k] = u[d];
             }
         }
         if (ma.partials) {

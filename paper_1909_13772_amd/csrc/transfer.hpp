@@ -124,11 +124,14 @@ private:
 // that cannot be had are done without.
 class HostCopy {
 public:
+    static constexpr size_t kMinToHost = (size_t)4 << 20, kMinToDevice = (size_t)128 << 20;
     HostCopy(PinnedRing &ring, bool to_host, hipStream_t st, size_t total) : ring_(ring), to_host_(to_host), st_(st)
     {
-        // a smaller transfer to the device is over (25 GB/s from pageable
-        // memory) before buffers and threads have paid for themselves
-        if (!to_host && total < ((size_t)128 << 20)) return;
+        // a smaller transfer is over before buffers and threads have paid for
+        // themselves, at 25 GB/s from pageable memory and some 15 into it (us
+        // by the runtime's own copy / through the buffers: density of 48^3, 0.9
+        // MB, 64 / 113, of 64^3, 2.1 MB, 143 / 170, of 80^3, 4.1 MB, 246 / 225)
+        if (total < (to_host ? kMinToHost : kMinToDevice)) return;
         chunk_ = std::min(PinnedRing::kChunk, std::max<size_t>((size_t)256 << 10, total / 4));
         chunk_ = (chunk_ + 4095) & ~(size_t)4095;
         pinned_ = ring.reserve(chunk_, st);
@@ -146,6 +149,8 @@ public:
         cv_.notify_all();
         for (int k = 0; k < n_workers_; ++k) workers_[k].join();
     }
+    // Whether pageable arrays go through the pinned buffers.
+    bool buffered() const { return pinned_; }
     // Memory the runtime knows (pinned or registered by the caller, managed,
     // device): the copy engine reads and writes it itself.
     static bool mapped(const void *p)

@@ -135,8 +135,9 @@ struct SweepArgs {
 struct MomArgs {
     SweepArgs s;
     int32_t swapped;       // 1: layout after an even sweep (read like the odd sweep)
-    int32_t z0, z1;        // global z range written to out (out == nullptr: none)
-    double *out;           // [4][ncells of slab]: rho, ux, uy, uz in global order of the slab
+    int32_t z0, z1;        // global z range written out
+    double *rho, *u;       // density [ncells of slab] and velocity [3][ncells of slab] in global
+                           // order of the slab; nullptr: not wanted
     double *partials;      // [ntiles][8] or nullptr
 };
 

@@ -32,7 +32,7 @@ static char *known = nullptr;
 static size_t known_bytes = 0;
 static bool is_known(const void *p) { return known && (const char *)p >= known && (const char *)p < known + known_bytes; }
 
-static std::atomic<int> n_copies{0}, n_known{0};
+static std::atomic<int> n_copies{0}, n_known{0}, n_pinned{0};
 static const std::thread::id main_thread = std::this_thread::get_id();
 
 // two devices; a stream's handle is 1000 times its device (0: the null stream)
@@ -47,7 +47,7 @@ hipError_t hipGetDevice(int *d) { return *d = device, hipSuccess; }
 hipError_t hipSetDevice(int d) { return device = d, hipSuccess; }
 hipError_t hipStreamGetDevice(hipStream_t st, hipDevice_t *d) { return *d = device_of(st), hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return ++n_pinned, (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostFree(void *p) { return free(p), hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return *e = (hipEvent_t)malloc(sizeof(Event)), ((Event *)*e)->device = device, hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { return free(e), hipSuccess; }
@@ -130,6 +130,28 @@ static void known_memory()
     }
 }
 
+// A transfer to the host below kMinToHost is left to the runtime: one copy
+// per array, to its place, and no buffers.
+static void small_transfers()
+{
+    PinnedRing ring;
+    for (size_t n : {(size_t)885 * 1000, HostCopy::kMinToHost - 1, HostCopy::kMinToHost}) {
+        char *dev = (char *)malloc(n), *host = (char *)calloc(n, 1);
+        memset(dev, 3, n);
+        known = nullptr;
+        n_copies = n_pinned = 0;
+        {
+            HostCopy c(ring, true, nullptr, n);
+            if (c.add(host, dev, n) != hipSuccess || c.flush() != hipSuccess) bad("add");
+        }
+        if (memcmp(host, dev, n)) bad("contents");
+        const bool small = n < HostCopy::kMinToHost;
+        if (small ? n_copies != 1 || n_pinned != 0 : n_pinned == 0) bad(small ? "a small transfer takes buffers" : "no buffers");
+        free(dev);
+        free(host);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
@@ -146,6 +168,7 @@ int main(int argc, char **argv)
         }
     }
     else if (!strcmp(what, "known_memory")) known_memory();
+    else if (!strcmp(what, "small_transfers")) small_transfers();
     else bad("unknown check");
     puts("ok");
 }

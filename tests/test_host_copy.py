@@ -49,3 +49,7 @@ def test_streams_of_another_device(check):
 def test_pinned_arrays_are_copied_in_place(check):
     """Arrays that the runtime knows go over the link as they are."""
     check("known_memory")
+
+
+def test_small_transfers_take_no_buffers(check):
+    check("small_transfers")
