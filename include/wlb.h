@@ -43,8 +43,10 @@
  *     during the call.  Device memory is one arena that the caller allocates
  *     (size from wlb_blocks_create) and binds; the library never allocates
  *     or frees device memory.  The handle owns host-side descriptors, the
- *     captured HIP graphs, the tuning state and up to 40 MB of pinned host
- *     memory for transfers, all given back by wlb_blocks_destroy.  A large
+ *     captured HIP graphs and the tuning state, all given back by
+ *     wlb_blocks_destroy.  The handles of a process share pinned host memory
+ *     for their transfers: up to 40 MB for each transfer under way and up to 82
+ *     MB kept between transfers, given back with the last handle.  A large
  *     transfer runs up to seven copying threads of its own until it returns.
  *   Streams: all device work is enqueued on the stream given to
  *     wlb_blocks_bind.  Calls that return host data synchronise that stream.

@@ -139,7 +139,7 @@ struct wlb_blocks {
     bool tiles_split = false;
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    PinnedRing ring;  // pinned buffers of the host transfers
+    PinnedPool::User pool_user;  // pinned buffers of the host transfers are kept meanwhile
     bool use_graph = true;
     // captured step pairs: graphs of one pair and of kGraphPairs pairs
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
@@ -781,16 +781,18 @@ struct Sums {
     double *at;
     bool host;
 };
-Sums sums_target(wlb_blocks *h)
+Sums sums_target(wlb_blocks *h, RingLease &lease)
 {
-    if (double *p = h->ring.sums(h->stream)) return Sums{p, true};
+    PinnedRing *r = lease.get();
+    if (double *p = r ? r->sums(h->stream) : nullptr) return Sums{p, true};
     return Sums{reinterpret_cast<double *>(h->arena + h->off_totals), false};
 }
 // Waits for the stream and hands the sums out.
-int sums_fetch(wlb_blocks *h, const Sums &s, double *out8)
+int sums_fetch(wlb_blocks *h, RingLease &lease, const Sums &s, double *out8)
 {
     if (!s.host) HIPCHK(hipMemcpyAsync(out8, s.at, 8 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
+    lease.idle();
     if (s.host) std::memcpy(out8, s.at, 8 * sizeof(double));
     return WLB_OK;
 }
@@ -808,9 +810,10 @@ int compute_totals(wlb_blocks *h, double *host8)
     m.z1 = 0;
     m.partials = partials_of(h);
     HIPCHK(moments_dispatch(h, m, aux_grid(h)));
-    const Sums tot = sums_target(h);
+    RingLease lease(h->stream);
+    const Sums tot = sums_target(h, lease);
     HIPCHK(launch_reduce_totals(m.partials, (int)h->tiles.size(), groups_of(h), tot.at, h->stream));
-    const int rc = sums_fetch(h, tot, host8);
+    const int rc = sums_fetch(h, lease, tot, host8);
     if (rc) return rc;
     host8[7] = (double)h->steps;
     return WLB_OK;
@@ -843,7 +846,8 @@ int do_init_state(wlb_blocks *h, const double *rho, const double *u)
     const int64_t N = plane * h->dom[2];
     const int kz = planes_per_chunk(h, 4 * sizeof(double));
     double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
-    HostCopy up(h->ring, false, h->stream, 4 * sizeof(double) * N);
+    RingLease lease(h->stream);
+    HostCopy up(lease, false, 4 * sizeof(double) * N);
     for (int z0 = 0; z0 < h->dom[2]; z0 += kz) {
         const int z1 = std::min(h->dom[2], z0 + kz);
         const int64_t S = (int64_t)(z1 - z0) * plane;
@@ -853,6 +857,7 @@ int do_init_state(wlb_blocks *h, const double *rho, const double *u)
         HIPCHK(init_dispatch(h, stage, z0, z1, aux_grid(h)));
     }
     HIPCHK(hipStreamSynchronize(h->stream));
+    lease.idle();
     h->steps = 0;
     h->parity = 0;
     h->pending = 0;
@@ -1604,13 +1609,6 @@ int wlb_blocks_bind(wlb_blocks_t h, void *arena, size_t bytes, void *stream)
     HIPCHK(hipMemcpyAsync(h->arena + h->off_push, h->push.data(), h->push.size() * sizeof(XItem),
                           hipMemcpyHostToDevice, h->stream));
     h->bound = true;
-    // pinned buffers of the field and population transfers (0.2 ms; the first
-    // transfer would pay for them otherwise), failing which copies go direct
-    if (small_fields(h))
-        (void)h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1, h->stream);
-    else
-        (void)h->ring.reserve(PinnedRing::kChunk, h->stream);
-    (void)h->ring.sums(h->stream);
     if (h->overlap) {
         int rc = ensure_stream2(h);
         if (rc) return rc;
@@ -1874,10 +1872,13 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
     // (32^3: 1 MB; four copies of 256 KB cost 14 us each), into pinned arrays
     // of the caller's by copies from 1 MB on (40^3: 115 us against 121).
     const bool mapped = (!rho || HostCopy::mapped(rho)) && (!u || HostCopy::mapped(u));
-    const bool direct = whole && small_fields(h) && !(mapped && field_bytes(h) > ((size_t)1 << 20)) &&
-                        h->ring.reserve(field_bytes(h) / PinnedRing::kSlots + 1, h->stream);
-    if (direct) stage = reinterpret_cast<double *>(h->ring.slot(0));
-    const Sums tot = sums_target(h);
+    RingLease lease(h->stream);
+    char *pinned = nullptr;
+    if (whole && small_fields(h) && !(mapped && field_bytes(h) > ((size_t)1 << 20)))
+        if (PinnedRing *r = lease.get()) pinned = r->bytes(field_bytes(h), h->stream);
+    const bool direct = pinned != nullptr;
+    if (direct) stage = reinterpret_cast<double *>(pinned);
+    const Sums tot = totals && whole ? sums_target(h, lease) : Sums{};
     auto fields = [&](int z0, int z1) -> int {
         MomArgs m{};
         m.s = h->args;
@@ -1895,7 +1896,7 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
         const int rc = fields(0, h->dom[2]);
         if (rc) return rc;
     } else {
-        HostCopy down(h->ring, true, h->stream, ((rho ? 1 : 0) + (u ? 3 : 0)) * sizeof(double) * N);
+        HostCopy down(lease, true, ((rho ? 1 : 0) + (u ? 3 : 0)) * sizeof(double) * N);
         for (int z0 = 0; z0 < h->dom[2]; z0 += kz) {
             const int z1 = std::min(h->dom[2], z0 + kz);
             const int64_t S = (int64_t)(z1 - z0) * plane;
@@ -1907,11 +1908,12 @@ int wlb_moments_get(wlb_blocks_t h, double *rho, double *u, double totals[8])
         HIPCHK(down.flush());
     }
     if (totals && whole) {
-        const int rc = sums_fetch(h, tot, totals);
+        const int rc = sums_fetch(h, lease, tot, totals);
         if (rc) return rc;
         totals[7] = (double)h->steps;
     } else {
         HIPCHK(hipStreamSynchronize(h->stream));
+        lease.idle();
     }
     if (direct) {
         if (rho) std::memcpy(rho, stage, N * sizeof(double));
@@ -1926,9 +1928,10 @@ int wlb_force_get(wlb_blocks_t h, double out[8])
     if (!h->inited) return fail(WLB_ERR_STATE, "wlb_lbm_init must come first");
     if (h->steps == 0) return fail(WLB_ERR_STATE, "no step since wlb_lbm_init: the force is that of the last step");
     HIPCHK(force_dispatch(h, partials_of(h), aux_grid(h)));
-    const Sums tot = sums_target(h);
+    RingLease lease(h->stream);
+    const Sums tot = sums_target(h, lease);
     HIPCHK(launch_reduce_sum8(partials_of(h), (int)h->tiles.size(), groups_of(h), tot.at, h->stream));
-    return sums_fetch(h, tot, out);
+    return sums_fetch(h, lease, tot, out);
 }
 
 int wlb_debug_write_coverage(wlb_blocks_t h, int32_t odd, uint32_t *counts)
@@ -1972,7 +1975,8 @@ static int pdfs_io(wlb_blocks_t h, double *d, bool to_dev)
     const int64_t N = plane * h->dom[2];
     const int kz = planes_per_chunk(h, h->q * sizeof(double));
     double *stage = reinterpret_cast<double *>(h->arena + h->off_stage);
-    HostCopy link(h->ring, !to_dev, h->stream, h->q * sizeof(double) * N);
+    RingLease lease(h->stream);
+    HostCopy link(lease, !to_dev, h->q * sizeof(double) * N);
     for (int z0 = 0; z0 < h->dom[2]; z0 += kz) {
         const int z1 = std::min(h->dom[2], z0 + kz);
         const int64_t S = (int64_t)(z1 - z0) * plane;
@@ -1985,6 +1989,7 @@ static int pdfs_io(wlb_blocks_t h, double *d, bool to_dev)
     }
     HIPCHK(link.flush());
     HIPCHK(hipStreamSynchronize(h->stream));
+    lease.idle();
     if (to_dev) {
         h->parity = 0;
         h->pending = 0;

@@ -20,6 +20,7 @@
 #include <condition_variable>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <thread>
 
 namespace wlb {
@@ -47,8 +48,7 @@ private:
     int before_ = -1, dev_ = -1;
 };
 
-// Pinned buffers of one handle, allocated at its first transfer and released
-// with it (kSlots x kChunk = 40 MB at most).
+// Pinned buffers of one transfer at a time, kept for the next one (PinnedPool).
 class PinnedRing {
 public:
     static constexpr int kSlots = 10;
@@ -59,19 +59,24 @@ public:
         if (base_) (void)hipHostFree(base_);
         if (small_) (void)hipHostFree(small_);
     }
-    // Room for kSlots pieces of `chunk` bytes, one after the other, for
-    // transfers on `st`; false without pinned memory.
-    bool reserve(size_t chunk, hipStream_t st)
+    // At least n bytes for a transfer on `st`, n at most kSlots x kChunk; null
+    // without pinned memory.  More than 1 MB is the whole ring: the runtime
+    // takes 250 us for 2 to 10 MB, and 12 for 40 MB that it has had before.
+    char *bytes(size_t n, hipStream_t st)
     {
         const OnDeviceOf on(st);
-        chunk = (chunk + 4095) & ~(size_t)4095;
-        if (chunk > chunk_) {
+        if (n > n_) {
             if (base_) (void)hipHostFree(base_);
-            chunk_ = 0;
-            base_ = pinned(chunk * kSlots);
-            if (!base_) return false;
-            chunk_ = chunk;
+            n_ = n <= ((size_t)1 << 20) ? (n + 4095) & ~(size_t)4095 : kSlots * kChunk;
+            base_ = pinned(n_);
+            if (!base_) n_ = 0;
         }
+        return static_cast<char *>(base_);
+    }
+    // Events of the device of `st`, one per slot; false without.
+    bool events(hipStream_t st)
+    {
+        const OnDeviceOf on(st);
         if (on.device() != dev_) drop_events();
         dev_ = on.device();
         for (; n_ev_ < kSlots; ++n_ev_)
@@ -81,7 +86,6 @@ public:
             }
         return true;
     }
-    char *slot(int k) const { return static_cast<char *>(base_) + (size_t)k * chunk_; }
     hipEvent_t event(int k) const { return ev_[k]; }
     // A few words that kernels write their sums to; null without pinned memory.
     double *sums(hipStream_t st)
@@ -101,14 +105,102 @@ private:
     static void *pinned(size_t n)
     {
         void *p = nullptr;
-        if (hipHostMalloc(&p, n, hipHostMallocDefault) == hipSuccess) return p;
+        if (hipHostMalloc(&p, n, hipHostMallocPortable) == hipSuccess) return p;
         (void)hipGetLastError();
         return nullptr;
     }
     void *base_ = nullptr, *small_ = nullptr;
-    size_t chunk_ = 0;
+    size_t n_ = 0;
     hipEvent_t ev_[kSlots];
     int n_ev_ = 0, dev_ = -1;  // events, and the device they belong to
+};
+
+// The rings of the process that no transfer is using, at most kKeep (82 MB).
+// Handles share them, so that pinned memory does not grow with the number of
+// handles; concurrent transfers have a ring each.  All are given back with
+// the last handle.
+class PinnedPool {
+public:
+    static constexpr int kKeep = 2;
+    static PinnedPool &process()
+    {
+        static PinnedPool p;
+        return p;
+    }
+    // A handle counts as long as it has one of these.
+    struct User {
+        User() { process().users(1); }
+        ~User() { process().users(-1); }
+        User(const User &) = delete;
+        User &operator=(const User &) = delete;
+    };
+    PinnedRing *take()
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (n_ > 0) return kept_[--n_];
+        }
+        return new (std::nothrow) PinnedRing;
+    }
+    void give(PinnedRing *r)
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (users_ > 0 && n_ < kKeep) {
+                kept_[n_++] = r;
+                r = nullptr;
+            }
+        }
+        delete r;
+    }
+
+private:
+    void users(int d)
+    {
+        PinnedRing *out[kKeep];
+        int n = 0;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            users_ += d;
+            if (users_ == 0)
+                while (n_ > 0) out[n++] = kept_[--n_];
+        }
+        while (n > 0) delete out[--n];
+    }
+    std::mutex mu_;
+    PinnedRing *kept_[kKeep] = {};
+    int n_ = 0, users_ = 0;
+};
+
+// A ring for the transfers of one call on one stream, taken at its first use.
+// It goes back when nothing on the stream uses it any more: after idle(), or
+// after waiting for the stream where the call ended early.
+class RingLease {
+public:
+    explicit RingLease(hipStream_t st) : st_(st) {}
+    RingLease(const RingLease &) = delete;
+    RingLease &operator=(const RingLease &) = delete;
+    ~RingLease()
+    {
+        if (!ring_) return;
+        if (!idle_) (void)hipStreamSynchronize(st_);
+        PinnedPool::process().give(ring_);
+    }
+    // Null where not even the object can be had.
+    PinnedRing *get()
+    {
+        if (!ring_) ring_ = PinnedPool::process().take();
+        idle_ = false;
+        return ring_;
+    }
+    hipStream_t stream() const { return st_; }
+    // The stream has been waited for since the last use.
+    void idle() { idle_ = true; }
+
+private:
+    hipStream_t st_;
+    PinnedRing *ring_ = nullptr;
+    bool idle_ = false;
 };
 
 // One transfer of about `total` bytes in one direction on one stream, as any
@@ -125,7 +217,7 @@ private:
 class HostCopy {
 public:
     static constexpr size_t kMinToHost = (size_t)4 << 20, kMinToDevice = (size_t)128 << 20;
-    HostCopy(PinnedRing &ring, bool to_host, hipStream_t st, size_t total) : ring_(ring), to_host_(to_host), st_(st)
+    HostCopy(RingLease &lease, bool to_host, size_t total) : to_host_(to_host), st_(lease.stream())
     {
         // a smaller transfer is over before buffers and threads have paid for
         // themselves, at 25 GB/s from pageable memory and some 15 into it (us
@@ -134,7 +226,9 @@ public:
         if (total < (to_host ? kMinToHost : kMinToDevice)) return;
         chunk_ = std::min(PinnedRing::kChunk, std::max<size_t>((size_t)256 << 10, total / 4));
         chunk_ = (chunk_ + 4095) & ~(size_t)4095;
-        pinned_ = ring.reserve(chunk_, st);
+        ring_ = lease.get();
+        base_ = ring_ ? ring_->bytes(chunk_ * PinnedRing::kSlots, st_) : nullptr;
+        pinned_ = base_ && ring_->events(st_);
         if (!pinned_) return;
         cpu_set_t cs;
         const int cpus = sched_getaffinity(0, sizeof cs, &cs) == 0 ? CPU_COUNT(&cs) : 1;
@@ -173,8 +267,8 @@ public:
             if (!free_slot(k)) return err_;
             const size_t m = std::min(chunk_, n - o);
             if (to_host_) {
-                hipError_t e = hipMemcpyAsync(ring_.slot(k), static_cast<char *>(dev) + o, m, hipMemcpyDeviceToHost, st_);
-                if (e == hipSuccess) e = hipEventRecord(ring_.event(k), st_);
+                hipError_t e = hipMemcpyAsync(slot(k), static_cast<char *>(dev) + o, m, hipMemcpyDeviceToHost, st_);
+                if (e == hipSuccess) e = hipEventRecord(ring_->event(k), st_);
                 if (e != hipSuccess) return e;
             }
             {
@@ -258,8 +352,8 @@ private:
             --ready_;
             if (err_ == hipSuccess) {
                 lk.unlock();
-                hipError_t e = hipMemcpyAsync(w.dev, ring_.slot(k), w.n, hipMemcpyHostToDevice, st_);
-                if (e == hipSuccess) e = hipEventRecord(ring_.event(k), st_);
+                hipError_t e = hipMemcpyAsync(w.dev, slot(k), w.n, hipMemcpyHostToDevice, st_);
+                if (e == hipSuccess) e = hipEventRecord(ring_->event(k), st_);
                 lk.lock();
                 if (e != hipSuccess && err_ == hipSuccess) err_ = e;
             }
@@ -276,12 +370,12 @@ private:
         hipError_t e;
         if (to_host_) {
             populate(p.host, p.n);
-            e = hipEventSynchronize(ring_.event(p.slot));
-            if (e == hipSuccess) std::memcpy(p.host, ring_.slot(p.slot) + p.off, p.n);
+            e = hipEventSynchronize(ring_->event(p.slot));
+            if (e == hipSuccess) std::memcpy(p.host, slot(p.slot) + p.off, p.n);
         } else {
             // the buffer's previous piece may still be on its way to the device
-            e = hipEventSynchronize(ring_.event(p.slot));
-            if (e == hipSuccess) std::memcpy(ring_.slot(p.slot) + p.off, p.host, p.n);
+            e = hipEventSynchronize(ring_->event(p.slot));
+            if (e == hipSuccess) std::memcpy(slot(p.slot) + p.off, p.host, p.n);
         }
         lk.lock();
         if (e != hipSuccess && err_ == hipSuccess) err_ = e;
@@ -305,7 +399,10 @@ private:
         (void)madvise(reinterpret_cast<void *>(a), b - a, kPopulateWrite);
     }
 
-    PinnedRing &ring_;
+    char *slot(int k) const { return base_ + (size_t)k * chunk_; }
+
+    PinnedRing *ring_ = nullptr;
+    char *base_ = nullptr;
     const bool to_host_;
     hipStream_t st_;
     size_t chunk_ = 0;

@@ -32,7 +32,7 @@ static char *known = nullptr;
 static size_t known_bytes = 0;
 static bool is_known(const void *p) { return known && (const char *)p >= known && (const char *)p < known + known_bytes; }
 
-static std::atomic<int> n_copies{0}, n_known{0}, n_pinned{0};
+static std::atomic<int> n_copies{0}, n_known{0}, n_pinned{0}, n_alive{0}, n_waits{0};
 static const std::thread::id main_thread = std::this_thread::get_id();
 
 // two devices; a stream's handle is 1000 times its device (0: the null stream)
@@ -47,8 +47,9 @@ hipError_t hipGetDevice(int *d) { return *d = device, hipSuccess; }
 hipError_t hipSetDevice(int d) { return device = d, hipSuccess; }
 hipError_t hipStreamGetDevice(hipStream_t st, hipDevice_t *d) { return *d = device_of(st), hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return ++n_pinned, (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
-hipError_t hipHostFree(void *p) { return free(p), hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return ++n_pinned, ++n_alive, (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostFree(void *p) { return --n_alive, free(p), hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return ++n_waits, hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return *e = (hipEvent_t)malloc(sizeof(Event)), ((Event *)*e)->device = device, hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { return free(e), hipSuccess; }
 // a copying thread is delayed now and then, so that pieces end out of order
@@ -83,13 +84,14 @@ using namespace wlb;
 
 // Arrays of sizes around the pieces and parts, in both directions and through
 // one ring, arrive whole.
-static void round_trips(PinnedRing &ring, hipStream_t st)
+static void round_trips(hipStream_t st)
 {
     const size_t mb = (size_t)1 << 20;
     const size_t sizes[] = {1, 4095, 512 << 10, (512 << 10) + 1, 4 * mb - 8, 4 * mb, 4 * mb + 1, 63 * mb + 5};
     for (int k = 0; k < 4; ++k)
         for (bool to_host : {true, false}) {
-            HostCopy c(ring, to_host, st, 140 * mb);
+            RingLease lease(st);
+            HostCopy c(lease, to_host, 140 * mb);
             char *src[8], *dst[8];
             for (int i = 0; i < 8; ++i) {
                 src[i] = (char *)malloc(sizes[i]);
@@ -100,6 +102,7 @@ static void round_trips(PinnedRing &ring, hipStream_t st)
                 if (i == 4 && c.flush() != hipSuccess) bad("flush");
             }
             if (c.flush() != hipSuccess) bad("flush");
+            lease.idle();
             for (int i = 0; i < 8; ++i) {
                 if (memcmp(src[i], dst[i], sizes[i])) bad("contents");
                 free(src[i]);
@@ -112,7 +115,6 @@ static void round_trips(PinnedRing &ring, hipStream_t st)
 // whatever the others of the transfer are.
 static void known_memory()
 {
-    PinnedRing ring;
     const size_t n = ((size_t)9 << 20) + 3;
     char *dev = (char *)malloc(n), *other = (char *)malloc(n);
     known = (char *)calloc(n, 1);
@@ -120,7 +122,8 @@ static void known_memory()
     for (bool to_host : {true, false}) {
         n_copies = n_known = 0;
         memset(to_host ? dev : known, to_host ? 1 : 2, n);
-        HostCopy c(ring, to_host, nullptr, (size_t)140 << 20);
+        RingLease lease(nullptr);
+        HostCopy c(lease, to_host, (size_t)140 << 20);
         if (c.add(known, dev, n) != hipSuccess || c.flush() != hipSuccess) bad("add");
         if (n_copies != 1 || n_known != 1) bad("a known array is copied through buffers");
         if (memcmp(known, dev, n)) bad("contents");
@@ -134,14 +137,14 @@ static void known_memory()
 // per array, to its place, and no buffers.
 static void small_transfers()
 {
-    PinnedRing ring;
     for (size_t n : {(size_t)885 * 1000, HostCopy::kMinToHost - 1, HostCopy::kMinToHost}) {
         char *dev = (char *)malloc(n), *host = (char *)calloc(n, 1);
         memset(dev, 3, n);
         known = nullptr;
         n_copies = n_pinned = 0;
         {
-            HostCopy c(ring, true, nullptr, n);
+            RingLease lease(nullptr);
+            HostCopy c(lease, true, n);
             if (c.add(host, dev, n) != hipSuccess || c.flush() != hipSuccess) bad("add");
         }
         if (memcmp(host, dev, n)) bad("contents");
@@ -152,18 +155,68 @@ static void small_transfers()
     }
 }
 
+// The pinned buffers of the process: kept between transfers and shared by the
+// handles, one for each transfer under way, bounded, and gone with the last
+// handle.
+static void pool()
+{
+    const size_t n = (size_t)20 << 20;
+    auto use = [&](RingLease &l) {
+        char *p = l.get()->bytes(n, nullptr);
+        if (!p || !l.get()->sums(nullptr)) bad("no buffer");
+        return p;
+    };
+    PinnedPool::User *a = new PinnedPool::User, *b = new PinnedPool::User;
+    if (n_pinned != 0) bad("pinned memory before the first transfer");
+    char *first;
+    {
+        RingLease l(nullptr);
+        first = use(l);
+        l.idle();
+    }
+    if (n_waits != 0) bad("waited for an idle stream");
+    {
+        RingLease l(nullptr);
+        if (use(l) != first) bad("the buffer is not kept");
+    }
+    if (n_waits != 1) bad("given back without waiting for the stream");
+    if (n_pinned != 2) bad("more than one buffer for transfers in turn");
+    {
+        RingLease l[5] = {RingLease(nullptr), RingLease(nullptr), RingLease(nullptr), RingLease(nullptr), RingLease(nullptr)};
+        char *p[5];
+        for (int k = 0; k < 5; ++k) {
+            p[k] = use(l[k]);
+            for (int j = 0; j < k; ++j)
+                if (p[j] == p[k]) bad("two transfers share a buffer");
+        }
+    }
+    if (n_alive != 2 * PinnedPool::kKeep) bad("the kept buffers are not bounded");
+    delete a;
+    if (n_alive == 0) bad("a handle that is left lost the buffers");
+    RingLease late(nullptr);
+    use(late);
+    delete b;
+    if (n_alive != 2) bad("buffers outlive the last handle");
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
-    PinnedRing ring;
-    if (!strcmp(what, "round_trips")) round_trips(ring, nullptr);
+    if (!strcmp(what, "pool")) {
+        pool();  // ends with a transfer that outlives its handle
+        if (n_alive != 0) bad("buffers are left");
+        puts("ok");
+        return 0;
+    }
+    PinnedPool::User handle;
+    if (!strcmp(what, "round_trips")) round_trips(nullptr);
     else if (!strcmp(what, "no_memory")) {
         no_memory = true;
-        round_trips(ring, nullptr);
+        round_trips(nullptr);
     }
     else if (!strcmp(what, "devices")) {
         for (int d : {1, 0, 1}) {
-            round_trips(ring, (hipStream_t)(uintptr_t)(1000 * d + 1));
+            round_trips((hipStream_t)(uintptr_t)(1000 * d + 1));
             if (device != 0) bad("the caller's device has changed");
         }
     }

@@ -70,3 +70,45 @@ def test_populations_and_initial_fields_from_any_memory(dom):
             assert np.array_equal(a, b), (pin_in, pin_out)
     finally:
         B.close()
+
+
+def test_handles_of_several_threads_share_the_buffers():
+    """Four handles, a thread and a stream each, step and fetch at the same
+    time, and are closed and made anew meanwhile: every fetch is what the
+    handle alone gives."""
+    import threading
+
+    say("case host threads")
+    doms = [(20, 20, 20), (64, 60, 62), (90, 91, 92), (130, 65, 67)]
+    want, got, errors = {}, {}, []
+
+    def work(dom, out):
+        try:
+            rho, u = inputs.random_state(dom, seed=dom[0], umag=0.01)
+            out[dom] = []
+            for _ in range(3):
+                B = wlb.Blocks(wlb.single_block(dom), dom, (1, 1, 1), stencil=19, storage=wlb.F32)
+                try:
+                    B.init(wlb.TRT, wlb.make_params(tau=0.8), rho, u)
+                    for n in (3, 2):
+                        B.step(n)
+                        r, v, t = B.moments()
+                        d = B.pdfs_get()
+                        B.pdfs_set(d)
+                        out[dom].append((r, v, t, d, B.moments()[1]))
+                finally:
+                    B.close()
+        except Exception as e:  # noqa: BLE001
+            errors.append((dom, e))
+
+    for d in doms:
+        work(d, want)
+    th = [threading.Thread(target=work, args=(d, got)) for d in doms]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    assert not errors, errors
+    for d in doms:
+        for a, b in zip(want[d], got[d]):
+            assert all(np.array_equal(x, y) for x, y in zip(a, b)), d

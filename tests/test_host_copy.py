@@ -53,3 +53,10 @@ def test_pinned_arrays_are_copied_in_place(check):
 
 def test_small_transfers_take_no_buffers(check):
     check("small_transfers")
+
+
+def test_pinned_buffers_are_shared_and_bounded(check):
+    """Handles cost no pinned memory, transfers in turn share one buffer, at
+    most two are kept, none outlives the last handle, and none goes back while
+    a stream may still use it."""
+    check("pool")
