@@ -358,17 +358,28 @@ void update_lds_stride(wlb_blocks *h)
 }
 
 // Strips over one descriptor's cells in x, y, z order, W places per row.
-void strip_region(const DevBlock &D, int b, int64_t W, std::vector<int4> &out)
+void strip_region(const DevBlock &D, int b, int W, std::vector<int4> &out)
 {
-    const int64_t n1 = D.n[1], cells = W * n1 * D.n[2];
+    const int n1 = D.n[1];
+    const int64_t cells = (int64_t)W * n1 * D.n[2];
+    out.reserve(out.size() + (size_t)((cells + kWG - 1) / kWG));
+    int x = 0, y = 0, z = 0;  // the strip's first place
     for (int64_t s = 0; s < cells; s += kWG) {
-        const int64_t count = std::min<int64_t>(kWG, cells - s);
-        const int64_t r0 = s / W, r1 = (s + count - 1) / W;  // rows touched
-        const int64_t y0 = r0 % n1, z0 = r0 / n1, y1 = r1 % n1, z1 = r1 / n1;
-        // rows y0 .. y1 of plane z0 = z1, or the end of z0 and the start of z1
-        const bool ylo = y0 == 0 || z1 > z0, yhi = y1 == n1 - 1 || z1 > z0;
-        const bool edge = (D.wylo && ylo) || (D.wyhi && yhi) || (D.wzlo && z0 == 0) || (D.wzhi && z1 == D.n[2] - 1);
-        out.push_back(make_int4(b, (int)(s % W) | (int)(count << 16), (int)y0 | (edge ? kStripEdge : 0), (int)z0));
+        const int count = (int)std::min<int64_t>(kWG, cells - s);
+        const int yl = y + (x + count - 1) / W, z1 = z + yl / n1, y1 = yl % n1;  // row of the last place
+        // rows y .. y1 of plane z = z1, or the end of z and the start of z1
+        const bool ylo = y == 0 || z1 > z, yhi = y1 == n1 - 1 || z1 > z;
+        const bool edge = (D.wylo && ylo) || (D.wyhi && yhi) || (D.wzlo && z == 0) || (D.wzhi && z1 == D.n[2] - 1);
+        out.push_back(make_int4(b, x | (count << 16), y | (edge ? kStripEdge : 0), z));
+        x += count;
+        if (x >= W) {
+            y += x / W;
+            x %= W;
+            if (y >= n1) {
+                z += y / n1;
+                y %= n1;
+            }
+        }
     }
 }
 
