@@ -271,7 +271,7 @@ def main():
                     help="use the default tile shape (for profiler runs that should hold only the timed launches)")
     ap.add_argument("--lds-staging", type=int, choices=[0, 1, 2], default=None,
                     help="with --no-autotune: odd sweep direct (0), staged in LDS (1) or over row vectors (2)")
-    ap.add_argument("--slot-round", type=int, choices=[16384, 2048, 0], default=None,
+    ap.add_argument("--slot-round", type=int, choices=[16384, 2048, 1028, 0], default=None,
                     help="with --no-autotune: slot stride rounding in KiB of the population slots of 64 MiB or more "
                          "(headline and variant runs)")
     ap.add_argument("--nontemporal", type=str, default=None,

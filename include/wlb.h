@@ -256,9 +256,9 @@ typedef struct {
                                its aligned ones (populations with c_x = 0) */
     int32_t n_class_tiles;  /* classes of x-runs (by y extent) whose tile shape the autotuner
                                set apart from `tile` (0: one shape for every run) */
-    int32_t slot_round_kib; /* population slots of 64 MiB or more start on multiples of this
-                               many KiB (0: 256-byte alignment only; 1028: multiples of 1 MiB
-                               plus 4 KiB); chosen by the autotuner, 16384 otherwise */
+    int32_t slot_round_kib; /* slot stride of the populations as wlb_set_slot_round takes it
+                               (16384, 2048, 1028 or 0); chosen by the autotuner, 16384
+                               otherwise */
 } wlb_info_t;
 int wlb_info(wlb_blocks_t h, wlb_info_t *out);
 
@@ -292,9 +292,11 @@ int wlb_set_class_tiles(wlb_blocks_t h, int32_t y_extent, int32_t tx, int32_t ty
 
 /* Slot stride of the population storage (Sec. 4.2: the layout of the
  * fields): slots of 64 MiB or more start on multiples of `kib` KiB (16384,
- * 2048, or 0 = 256-byte alignment only); smaller slots keep their own
- * stride (with 16384, slots of 16 MiB or more a multiple of 1 MiB plus 4 KiB,
- * otherwise alignment only).
+ * 2048, or 0 = 256-byte alignment only), or with 1028 on multiples of 1 MiB
+ * plus 4 KiB where that is no more than the next multiple of 16 MiB.  Slots of
+ * 16 to 64 MiB start on multiples of 1 MiB plus 4 KiB with 16384 and 1028;
+ * otherwise, like smaller slots, they are aligned only.  The values are those
+ * that wlb_info_t.slot_round_kib reports.
  * The arena is sized for 16384, the default.  Call after wlb_blocks_bind and
  * before wlb_lbm_init; an init with the autotuner chooses the stride again.
  * Results do not depend on it.

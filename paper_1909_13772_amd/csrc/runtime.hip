@@ -73,8 +73,8 @@ struct wlb_blocks {
     int nblk = 0;
     std::vector<std::vector<int>> runs;
     // population slots: run_slot0[r] elements per slot of run r before the
-    // stride rounding; slots of 64 MiB or more are rounded up to a multiple
-    // of slot_round bytes (an autotuner candidate, see relayout_slots)
+    // stride is chosen; slots of 16 MiB or more get their stride from
+    // slot_round (an autotuner candidate, see slot_stride)
     std::vector<int64_t> run_slot0;
     // the runs are parts of one array over the domain (one entry in
     // run_slot0): faces between them are plain neighbouring elements, and the
@@ -2077,7 +2077,8 @@ int wlb_set_class_tiles(wlb_blocks_t h, int32_t y_extent, int32_t tx, int32_t ty
 int wlb_set_slot_round(wlb_blocks_t h, int32_t kib)
 {
     if (!h) return fail(WLB_ERR_ARG, "null handle");
-    if (kib != 16384 && kib != 2048 && kib != 0) return fail(WLB_ERR_ARG, "slot rounding must be 16384, 2048 or 0 KiB");
+    if (kib != 16384 && kib != 2048 && kib != 0 && kib != (int32_t)(kSlotSkew >> 10))
+        return fail(WLB_ERR_ARG, "slot rounding must be 16384, 2048, 1028 or 0 KiB");
     if (h->inited) return fail(WLB_ERR_STATE, "the slot stride is set before wlb_lbm_init");
     relayout_slots(h, (size_t)kib << 10);
     if (h->bound) {
