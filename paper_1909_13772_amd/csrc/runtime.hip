@@ -1037,7 +1037,19 @@ int autotune(wlb_blocks *h)
     for (int64_t s0 : h->run_slot0) big = big || s0 * h->esize >= ((int64_t)16 << 20);
     if (big) {
         size_t bround = h->slot_round;
-        for (size_t cand : {(size_t)2 << 20, (size_t)0, kSlotSkew}) {
+        // candidates that give every run the stride of another one are that
+        // one: noise would choose between them, and the reported value be wrong
+        const size_t cands[] = {h->slot_round, (size_t)0, (size_t)2 << 20, kSlotSkew};
+        auto same = [&](size_t a, size_t b) {
+            for (int64_t s0 : h->run_slot0)
+                if (slot_stride((size_t)s0 * h->esize, a) != slot_stride((size_t)s0 * h->esize, b)) return false;
+            return true;
+        };
+        for (int c = 1; c < 4; ++c) {
+            const size_t cand = cands[c];
+            bool timed = false;
+            for (int k = 0; k < c; ++k) timed = timed || same(cands[k], cand);
+            if (timed) continue;
             relayout_slots(h, cand);
             HIPCHK(hipMemcpyAsync(h->arena + h->off_blocks, h->dev.data(), h->dev.size() * sizeof(DevBlock),
                                   hipMemcpyHostToDevice, h->stream));

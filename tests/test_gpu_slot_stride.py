@@ -45,3 +45,23 @@ def test_every_stride_gives_the_same_bits(dom, storage):
             B.close()
         ref = got if ref is None else ref
         assert all(np.array_equal(a, b) for a, b in zip(got, ref)), kib
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dom,strides", [((168, 160, 157), [0]),  # 17 MiB: 16384 and 1028 are one layout, 2048 and 0 another
+                                         ((256, 255, 256), [0, 2048, 1028]),  # 64.75 MiB
+                                         ((256, 254, 254), []),  # 64 MiB, a multiple of 16 MiB already
+                                         ((64, 50, 50), [])])
+def test_autotuner_measures_each_layout_once(dom, strides, monkeypatch, capfd):
+    say(f"case tuned strides {dom}")
+    monkeypatch.setenv("WLB_AUTOTUNE_LOG", "1")
+    rho, u = inputs.uniform_state(dom)
+    B = wlb.Blocks(wlb.single_block(dom), dom, (1, 1, 1), stencil=19, storage=wlb.F32)
+    try:
+        B.init(wlb.TRT, wlb.make_params(tau=0.8, autotune=1), rho, u)
+        got = B.info().slot_round_kib
+    finally:
+        B.close()
+    err = capfd.readouterr().err
+    tried = [int(line.split("rounding")[1].split("KiB")[0]) for line in err.splitlines() if "slot stride rounding" in line]
+    assert tried == strides and got in strides + [16384]
