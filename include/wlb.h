@@ -246,8 +246,9 @@ typedef struct {
     int32_t grid;           /* workgroups per sweep launch (0 = one per tile, -1 = one per tile
                                with XCD-contiguous tile ranges) */
     int32_t lds_staging;    /* odd-sweep kernel in use: 0 direct, 1 LDS-staged, 2 row vectors */
-    int32_t n_xchg_items;   /* exchange work items per exchange */
-    int64_t xchg_elems;     /* populations copied per exchange */
+    int32_t n_xchg_items;   /* exchange work items per exchange, and the populations it copies: 0 */
+    int64_t xchg_elems;     /* where the sweeps cross the faces themselves.  Before wlb_blocks_bind:
+                               the items and populations that cross faces of blocks or periodic ones */
     size_t arena_bytes;
     size_t pop_bytes;       /* bytes of population storage incl. ghosts */
     int32_t overlap;        /* 1: sweeps split into interior and frontier, exchange overlapped */

@@ -82,7 +82,11 @@ struct wlb_blocks {
     bool unified = false;
     bool ghost_stale = false;   // the last even sweep's exchange was left out (it wrapped in place)
     bool last_wrapped = false;  // the last sweep wrapped in place
-    int32_t n_xitems = 0;       // exchange items per exchange
+    // faces between blocks and periodic faces: work items and populations that
+    // cross them; xchg_kept: the populations of the items that are left in
+    // pull and push (with one array, those around the domain)
+    int32_t n_xitems = 0;
+    int64_t xchg_kept = 0;
     size_t slot_round = (size_t)16 << 20;
     std::vector<HostBlock> rhost;  // extent and y/z neighbour flags of each run
     std::vector<TileHost> tiles;
@@ -1588,6 +1592,7 @@ int wlb_blocks_create(const wlb_block_desc *d, int32_t n, const int32_t domain[3
         h->pull.erase(std::remove_if(h->pull.begin(), h->pull.end(), same), h->pull.end());
         h->push.erase(std::remove_if(h->push.begin(), h->push.end(), same), h->push.end());
     }
+    for (const XItem &it : h->pull) h->xchg_kept += it.count;
     h->off_pull = off;
     off += round_up(h->pull.size() * sizeof(XItem) + 1, 256);
     h->off_push = off;
@@ -2047,8 +2052,11 @@ int wlb_info(wlb_blocks_t h, wlb_info_t *o)
     o->overlap = split_sweeps(h) ? 1 : 0;
     o->nt_even = h->nt_even ? 1 : 0;
     o->nt_odd = h->nt_odd;
-    o->n_xchg_items = h->n_xitems;
-    o->xchg_elems = h->xchg_elems;
+    // until the sweeps are known (bind), what crosses the faces; then what an
+    // exchange copies, nothing where the sweeps cross the faces themselves
+    const bool none = h->bound && wraps_in_place(h);
+    o->n_xchg_items = !h->bound ? h->n_xitems : none ? 0 : (int32_t)h->pull.size();
+    o->xchg_elems = !h->bound ? h->xchg_elems : none ? 0 : h->xchg_kept;
     o->arena_bytes = h->arena_bytes;
     o->pop_bytes = h->pop_bytes;
     return WLB_OK;

@@ -4,6 +4,7 @@ the other odd-sweep kernels and the oracle."""
 import numpy as np
 import pytest
 
+import oracle as O
 from gpu_util import gpu_run, oracle_params, oracle_run, pop_err, rel_l2, say
 from paper_1909_13772_amd import inputs, wlb
 
@@ -138,5 +139,49 @@ def test_health_check_stops_a_diverging_run_at_its_step():
         with pytest.raises(wlb.WlbError) as e:
             B.step(100)
         assert e.value.code == wlb.WLB_ERR_DIVERGED and B.info().steps == 20
+    finally:
+        B.close()
+
+
+def test_info_reports_the_exchange_that_runs():
+    """Nothing where the sweeps cross the faces themselves, the ghost layer
+    around the domain for the LDS-staged odd sweep, every face between
+    separate arrays."""
+    def crossing(n, axes, q):
+        """Populations that leave a box of n cells across a y or z face (x
+        wraps inside the rows)."""
+        c = np.asarray(O.stencil(q)[0])[:q]
+        cells = np.stack(np.meshgrid(*[np.arange(v) for v in n], indexing="ij"), -1).reshape(-1, 3)
+        out = 0
+        for e in c:
+            t = cells + e
+            m = np.zeros(len(cells), bool)
+            for a in axes:
+                m |= (t[:, a] < 0) | (t[:, a] >= n[a])
+            out += int(m.sum())
+        return out
+
+    dom = (32, 20, 12)
+    blocks, _ = inputs.rectilinear_blocks([16, 16], [8, 12], [12])
+    rho, u = inputs.uniform_state(dom)
+    B = wlb.Blocks(blocks, dom, (1, 1, 1), stencil=19, storage=wlb.F64)
+    try:
+        B.init(wlb.TRT, wlb.make_params(tau=0.8), rho, u)
+        assert (B.info().n_xchg_items, B.info().xchg_elems) == (0, 0)
+        B.set_lds_staging(1)
+        assert B.info().lds_staging == 1 and B.info().xchg_elems == crossing(dom, (1, 2), 19)
+        B.set_kernel_timing(True)
+        B.step(2)
+        assert B.kernel_times()[1][2:] == [1, 1] and B.info().n_xchg_items > 0
+        B.set_lds_staging(0)
+        assert (B.info().n_xchg_items, B.info().xchg_elems) == (0, 0)
+    finally:
+        B.close()
+    dom = (2, 2400, 2400)
+    blocks, _ = inputs.rectilinear_blocks([2], [1000, 1400], [2400])
+    B = wlb.Blocks(blocks, dom, (1, 1, 1), stencil=9, storage=wlb.F32)
+    try:
+        # two faces along y between the two arrays, six populations of D2Q9 each
+        assert B.info().n_xchg_items > 0 and B.info().xchg_elems == 2 * 6 * 2 * 2400
     finally:
         B.close()
