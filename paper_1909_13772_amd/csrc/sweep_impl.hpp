@@ -1447,13 +1447,16 @@ __device__ __forceinline__ void store_regular_out(const SweepArgs &a, const DevB
 // to D3Q19 (at most 80 VGPRs): they are bound by vector instructions and
 // latency, which the extra wavefronts hide (256^3 channel: FP16 48.9k ->
 // 51.3k MLUPS); D3Q27 spills there and takes the compiler's own allocation.
-// At most 3 for the FP64 even sweep up to D3Q19: bound by its accesses, it
-// gains nothing from a fourth and loses order in memory (256^3 channel 897 ->
-// 873 us, 200^3 468 -> 447 us).  Elsewhere the compiler's own allocation.
+// At most 3 for the FP64 even sweep of D3Q19 with the hint, that is where the
+// populations stream: bound by its accesses, it gains nothing from a fourth and
+// loses order in memory (us per even sweep, three / the compiler's own four:
+// 256^3 channel 871 / 895, 250 x 150 x 190 407 / 418; not so D2Q9, 4000 x 2000
+// 217 / 200, and D3Q15, 160^3 171 / 165; and from the caches, 64^3 D3Q19, a
+// step of 14.3 / 14.0).  Elsewhere the compiler's own allocation.
 template <int Q, typename ST>
 constexpr int kWavesMin = (kStochastic<ST> && Q <= 19) ? 6 : 1;
-template <int Q, typename ST, bool ODD>
-constexpr int kWavesMax = (std::is_same_v<ST, double> && Q <= 19 && !ODD) ? 3 : 8;
+template <int Q, typename ST, bool ODD, bool NT>
+constexpr int kWavesMax = (std::is_same_v<ST, double> && Q == 19 && !ODD && NT) ? 3 : 8;
 // NT: the population accesses carry the non-temporal hint (the autotuner
 // chooses it per parity).
 // AO: the odd sweep's hint on its aligned accesses only (nt_shifted).
@@ -1513,7 +1516,7 @@ __device__ __forceinline__ void sweep_tiles(const SweepArgs &a)
 }
 
 template <int Q, int COLL, typename ST, bool ODD, bool NT, int CL>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(kWavesMin<Q, ST>, kWavesMax<Q, ST, ODD>))) void
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(kWavesMin<Q, ST>, kWavesMax<Q, ST, ODD, NT>))) void
 sweep_kernel(const SweepArgs a)
 {
     sweep_tiles<Q, COLL, ST, ODD, NT, false, CL>(a);
@@ -1523,7 +1526,7 @@ sweep_kernel(const SweepArgs a)
 // populations with c_x = 0); an autotuner candidate beside the odd sweep
 // with the hint on every access and the one without it.
 template <int Q, int COLL, typename ST, int CL>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(kWavesMin<Q, ST>, kWavesMax<Q, ST, true>))) void
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(kWavesMin<Q, ST>, kWavesMax<Q, ST, true, true>))) void
 sweep_odd_aligned_nt_kernel(const SweepArgs a)
 {
     sweep_tiles<Q, COLL, ST, true, true, true, CL>(a);
