@@ -270,7 +270,8 @@ int wlb_info(wlb_blocks_t h, wlb_info_t *out);
  * neighbouring tiles share an L2; > 0 = a persistent grid of that many
  * workgroups looping over the tiles.  tx = 0 packs whole x rows (the sweeps
  * then run over strips of 256 consecutive cells unless the LDS-staged odd
- * sweep, the overlap or per-class shapes need boxes); tx = -1
+ * sweep, the overlap or per-class shapes need boxes, or the odd sweep hints
+ * every access and rows are not whole wavefronts of 64 cells); tx = -1
  * makes the sweeps run over lists of up to 256 fluid cells of one block
  * (no lanes on solid cells; needs a preceding wlb_lbm_init with solid cells
  * and blocks of at most 1024 x 1024 x 4096 cells), all other passes over
@@ -344,8 +345,9 @@ int wlb_set_overlap(wlb_blocks_t h, int32_t on);
 
 /* Non-temporal hint (1) or ordinary cached accesses (0) for the population
  * loads and stores of the even and of the odd sweep (until set here or by the
- * autotuner: chosen by size and storage type); for the odd sweep also 2: the hint on its aligned accesses only (the populations with
- * c_x = 0, whole lines per wavefront), the others cached.  Streamed once per
+ * autotuner: chosen by size and storage type); for the odd sweep also 2: the
+ * hint on its aligned accesses only (the populations with c_x = 0, whole lines
+ * per wavefront), the others cached.  Streamed once per
  * sweep, the populations usually gain from the hint; accesses one element
  * off the row alignment, and short rows whose cache lines neighbouring waves
  * share, can gain from the cache instead.  Results are bitwise identical

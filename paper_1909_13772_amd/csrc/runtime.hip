@@ -344,14 +344,20 @@ void update_lds_stride(wlb_blocks *h)
     // places, which leave few lanes idle whatever the row length (box tiles of
     // whole rows hold 160 of 256 lanes at rows of 160 cells, 320 of 512 at
     // 320); the LDS-staged odd sweep and the interior / frontier split need
-    // boxes.
+    // boxes.  So does the odd sweep hinted on every access, unless a row is
+    // whole wavefronts: where wavefronts end inside a row at another place in
+    // each, more lines are shared by two and fetched twice (us per step with
+    // the hints 1, 1, strips / boxes: 200^3 FP32 308 / 283, FP64 516 / 491,
+    // 130^3 FP16 86 / 72; rows of 320 cells, FP16, 174 / 193).
     SweepArgs &a = h->args;
+    const bool shared = h->nt_odd == 1 && h->dom[0] % 64 != 0;
     a.strip = 0;
     if (!h->bound) return;
     if (h->list_mode) {
         a.stiles = reinterpret_cast<const int4 *>(h->arena + h->off_ltiles);
         a.nstiles = (int)h->ltiles.size();
-    } else if (h->shape[0] == 0 && h->run_shape.empty() && !h->overlap && a.lds_stride == 0 && h->strip_row > 0) {
+    } else if (h->shape[0] == 0 && h->run_shape.empty() && !h->overlap && a.lds_stride == 0 && h->strip_row > 0 &&
+               !shared) {
         a.stiles = reinterpret_cast<const int4 *>(h->arena + h->off_strips);
         a.nstiles = (int)h->strips.size();
         a.strip = h->strip_row;
@@ -2116,7 +2122,7 @@ int wlb_set_nontemporal(wlb_blocks_t h, int32_t even, int32_t odd)
     if (odd < 0 || odd > 2) return fail(WLB_ERR_ARG, "odd-sweep hint must be 0, 1 or 2");
     h->nt_even = even != 0;
     h->nt_odd = odd;
-    h->graph_valid = false;  // the captured launches hold the old arguments
+    update_lds_stride(h);  // strips or boxes; the captured launches hold the old arguments
     return WLB_OK;
 }
 
