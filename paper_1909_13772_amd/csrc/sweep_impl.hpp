@@ -2128,12 +2128,15 @@ __global__ __launch_bounds__(kWG) void moments_kernel(const MomArgs ma)
 // every population, each thread sums its (y, z) column of factor^2 cells, and
 // the factor sums along x meet in LDS.  Bound by the one read of the
 // populations (256^3 FP32: 1.28 GB); with one thread per coarse cell, whose
-// lanes read elements `factor` apart, that case took 712 us.
+// lanes read elements `factor` apart, that case took 712 us.  ONE: factor 1,
+// whose sums need no LDS (192^3 FP16 D3Q19 210 -> 172 us; as a branch of the
+// general kernel it cost factor 16 half its speed).
 // ---------------------------------------------------------------------------
-template <int Q, typename ST, bool SWAPPED>
-__global__ __launch_bounds__(kWG) void filter_kernel(const SweepArgs a, int fac, double *out)
+template <int Q, typename ST, bool SWAPPED, bool ONE>
+__global__ __launch_bounds__(kWG) void filter_kernel(const SweepArgs a, int factor, double *out)
 {
-    __shared__ double sum[10][kWG];
+    __shared__ double sum[ONE ? 1 : 10][kWG];
+    const int fac = ONE ? 1 : factor;
     const DevBlock B = a.blocks[0];
     const int ncx = B.n[0] / fac, ncy = B.n[1] / fac, ncz = B.n[2] / fac;
     const int64_t Nc = (int64_t)ncx * ncy * ncz;
@@ -2180,16 +2183,21 @@ __global__ __launch_bounds__(kWG) void filter_kernel(const SweepArgs a, int fac,
                         acc[9] += u[1] * u[2];
                     }
         }
-        for (int k = 0; k < 10; ++k) sum[k][threadIdx.x] = acc[k];
-        __syncthreads();
-        for (int e = threadIdx.x; e < 10 * cells; e += kWG) {
-            const int g = e % cells, k = e / cells;
-            if (c0 + g >= Nc) continue;
-            double r = 0.0;
-            for (int d = 0; d < lanes; ++d) r += sum[k][g * lanes + d];
-            out[k * Nc + c0 + g] = r * inv;
+        if constexpr (ONE) {
+            if (c < Nc)
+                for (int k = 0; k < 10; ++k) out[k * Nc + c] = acc[k] * inv;
+        } else {
+            for (int k = 0; k < 10; ++k) sum[k][threadIdx.x] = acc[k];
+            __syncthreads();
+            for (int e = threadIdx.x; e < 10 * cells; e += kWG) {
+                const int g = e % cells, k = e / cells;
+                if (c0 + g >= Nc) continue;
+                double r = 0.0;
+                for (int d = 0; d < lanes; ++d) r += sum[k][g * lanes + d];
+                out[k * Nc + c0 + g] = r * inv;
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -2577,11 +2585,12 @@ hipError_t WLB_CAT(filter_, WLB_SUFFIX)(int q, const SweepArgs &a, int fac, doub
     if (g < 1) g = 1;
     return by_set(q, [&](auto S) {
         constexpr int Q = decltype(S)::value;
-        if (swapped)
-            hipLaunchKernelGGL((filter_kernel<Q, WLB_STORAGE, true>), dim3((int)g), dim3(kWG), 0, st, a, fac, out);
-        else
-            hipLaunchKernelGGL((filter_kernel<Q, WLB_STORAGE, false>), dim3((int)g), dim3(kWG), 0, st, a, fac, out);
-        return hipGetLastError();
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((int)g), dim3(kWG), 0, st, a, fac, out);
+            return hipGetLastError();
+        };
+        if (fac == 1) return swapped ? launch(filter_kernel<Q, WLB_STORAGE, true, true>) : launch(filter_kernel<Q, WLB_STORAGE, false, true>);
+        return swapped ? launch(filter_kernel<Q, WLB_STORAGE, true, false>) : launch(filter_kernel<Q, WLB_STORAGE, false, false>);
     });
 }
 
