@@ -173,8 +173,9 @@ private:
 };
 
 // A ring for the transfers of one call on one stream, taken at its first use.
-// It goes back when nothing on the stream uses it any more: after idle(), or
-// after waiting for the stream where the call ended early.
+// The call is over when nothing on the stream uses the ring or the caller's
+// arrays any more: after idle(), or after waiting for the stream where the call
+// ended early.
 class RingLease {
 public:
     explicit RingLease(hipStream_t st) : st_(st) {}
@@ -182,17 +183,18 @@ public:
     RingLease &operator=(const RingLease &) = delete;
     ~RingLease()
     {
-        if (!ring_) return;
         if (!idle_) (void)hipStreamSynchronize(st_);
-        PinnedPool::process().give(ring_);
+        if (ring_) PinnedPool::process().give(ring_);
     }
     // Null where not even the object can be had.
     PinnedRing *get()
     {
         if (!ring_) ring_ = PinnedPool::process().take();
-        idle_ = false;
+        busy();
         return ring_;
     }
+    // Something that uses the ring or the caller's arrays is on the stream.
+    void busy() { idle_ = false; }
     hipStream_t stream() const { return st_; }
     // The stream has been waited for since the last use.
     void idle() { idle_ = true; }
@@ -200,7 +202,7 @@ public:
 private:
     hipStream_t st_;
     PinnedRing *ring_ = nullptr;
-    bool idle_ = false;
+    bool idle_ = true;
 };
 
 // One transfer of about `total` bytes in one direction on one stream, as any
@@ -217,7 +219,7 @@ private:
 class HostCopy {
 public:
     static constexpr size_t kMinToHost = (size_t)4 << 20, kMinToDevice = (size_t)128 << 20;
-    HostCopy(RingLease &lease, bool to_host, size_t total) : to_host_(to_host), st_(lease.stream())
+    HostCopy(RingLease &lease, bool to_host, size_t total) : lease_(lease), to_host_(to_host), st_(lease.stream())
     {
         // a smaller transfer is over before buffers and threads have paid for
         // themselves, at 25 GB/s from pageable memory and some 15 into it (us
@@ -258,6 +260,7 @@ public:
     {
         // through the buffers pinned arrays would only be slower (populations
         // of 100^3, 152 MB: 3.7 ms against 3.2; density of 64^3: 163 us against 64)
+        lease_.busy();
         if (!pinned_ || mapped(host))
             return to_host_ ? hipMemcpyAsync(host, dev, n, hipMemcpyDeviceToHost, st_)
                             : hipMemcpyAsync(dev, host, n, hipMemcpyHostToDevice, st_);
@@ -401,6 +404,7 @@ private:
 
     char *slot(int k) const { return base_ + (size_t)k * chunk_; }
 
+    RingLease &lease_;
     PinnedRing *ring_ = nullptr;
     char *base_ = nullptr;
     const bool to_host_;

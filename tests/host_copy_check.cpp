@@ -30,6 +30,7 @@ void operator delete(void *p, size_t) noexcept { free(p); }
 // memory known to the runtime
 static char *known = nullptr;
 static size_t known_bytes = 0;
+static int fail_after = -1;  // copies that succeed before one fails (-1: all)
 static bool is_known(const void *p) { return known && (const char *)p >= known && (const char *)p < known + known_bytes; }
 
 static std::atomic<int> n_copies{0}, n_known{0}, n_pinned{0}, n_alive{0}, n_waits{0};
@@ -73,6 +74,7 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
 }
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind kind, hipStream_t)
 {
+    if (fail_after >= 0 && fail_after-- == 0) return hipErrorUnknown;
     n_known += is_known(kind == hipMemcpyDeviceToHost ? dst : src);
     if (std::this_thread::get_id() != main_thread) bad("a copy is enqueued by a copying thread");
     ++n_copies;
@@ -199,6 +201,33 @@ static void pool()
     if (n_alive != 2) bad("buffers outlive the last handle");
 }
 
+// A call that ends early waits for the stream: copies from and to the
+// caller's arrays may still be under way.
+static void early_end()
+{
+    const size_t n = (size_t)1 << 20;
+    char *dev = (char *)malloc(n);
+    known = (char *)calloc(n, 1);
+    known_bytes = n;
+    for (size_t total : {n, (size_t)200 << 20})
+        for (bool to_host : {true, false}) {
+            n_waits = 0;
+            fail_after = 1;
+            {
+                RingLease lease(nullptr);
+                HostCopy c(lease, to_host, total);
+                if (c.add(known, dev, n) != hipSuccess) bad("add");
+                if (c.add(known, dev, n) == hipSuccess) bad("a failed copy is not reported");
+            }
+            if (n_waits != 1) bad("returned while a copy may be under way");
+        }
+    n_waits = 0;
+    {
+        RingLease lease(nullptr);
+    }
+    if (n_waits != 0) bad("waited for nothing");
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
@@ -222,6 +251,7 @@ int main(int argc, char **argv)
     }
     else if (!strcmp(what, "known_memory")) known_memory();
     else if (!strcmp(what, "small_transfers")) small_transfers();
+    else if (!strcmp(what, "early_end")) early_end();
     else bad("unknown check");
     puts("ok");
 }

@@ -60,3 +60,8 @@ def test_pinned_buffers_are_shared_and_bounded(check):
     most two are kept, none outlives the last handle, and none goes back while
     a stream may still use it."""
     check("pool")
+
+
+def test_a_failed_transfer_waits_for_the_stream(check):
+    """After an error nothing still reads or writes the caller's arrays."""
+    check("early_end")
