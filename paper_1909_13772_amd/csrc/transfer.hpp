@@ -211,11 +211,11 @@ private:
 // take a quarter of their size), and a piece is copied on the host in parts
 // of 512 KB by whichever thread is free.  Arrays in memory that the runtime
 // knows are copied without buffers.  They are whole, like the others after
-// flush(), once the stream has been waited for.  Device-side order is the stream's: a
-// kernel launched before add() has finished when its pieces are read, and one
-// launched after flush() sees every piece written.  Nothing here throws, for
-// the C entry points that use it: its lists have a fixed size, and threads
-// that cannot be had are done without.
+// flush(), once the stream has been waited for.  Device-side order is the
+// stream's: a kernel launched before add() has finished when its pieces are
+// read, and one launched after flush() sees every piece written.  Nothing here
+// throws, for the C entry points that use it: its lists have a fixed size, and
+// threads that cannot be had are done without.
 class HostCopy {
 public:
     static constexpr size_t kMinToHost = (size_t)4 << 20, kMinToDevice = (size_t)128 << 20;
