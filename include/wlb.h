@@ -241,7 +241,7 @@ typedef struct {
     int32_t n_blocks;
     int64_t n_cells;        /* interior cells of all blocks */
     int64_t n_fluid;        /* fluid cells */
-    int32_t n_tiles;
+    int32_t n_tiles;        /* tiles of a sweep: strips, boxes or lists (before binding: boxes) */
     int32_t tile[3];        /* tile shape target in use (x, y, z); -1, 0, 0: fluid-cell lists */
     int32_t grid;           /* workgroups per sweep launch (0 = one per tile, -1 = one per tile
                                with XCD-contiguous tile ranges) */
